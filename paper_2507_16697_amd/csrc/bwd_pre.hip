@@ -42,15 +42,26 @@ __global__ __launch_bounds__(kPreThreads) void bwd_pre_bf16_kernel(
   }
 }
 
+// fp32: 16 lanes per row, consecutive lanes on consecutive dims.
+constexpr int kF32Tpr = 16;
 __global__ __launch_bounds__(kPreThreads) void bwd_pre_f32_kernel(
     const float* __restrict__ out, const float* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ delta, float* __restrict__ nl, int64_t rows, int d) {
-  const int64_t row = (int64_t)blockIdx.x * kPreThreads + threadIdx.x;
-  if (row >= rows) return;
-  float s = 0.f;
-  for (int c = 0; c < d; ++c) s = __builtin_fmaf(out[row * d + c], dout[row * d + c], s);
-  delta[row] = s;
-  nl[row] = lse[row] * -kLog2e;
+  const int part = threadIdx.x % kF32Tpr;
+  for (int64_t row0 = (int64_t)blockIdx.x * (kPreThreads / kF32Tpr); row0 < rows;
+       row0 += (int64_t)gridDim.x * (kPreThreads / kF32Tpr)) {
+    const int64_t row = row0 + threadIdx.x / kF32Tpr;
+    float s = 0.f;
+    if (row < rows)
+      for (int c = part; c < d; c += kF32Tpr)
+        s = __builtin_fmaf(out[row * d + c], dout[row * d + c], s);
+#pragma unroll
+    for (int off = kF32Tpr / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kF32Tpr);
+    if (row < rows && part == 0) {
+      delta[row] = s;
+      nl[row] = lse[row] * -kLog2e;
+    }
+  }
 }
 
 }  // namespace
@@ -69,7 +80,9 @@ hipError_t launch_bwd_pre(const BwdArgs& a, bool bf16) {
                          (const __bf16*)a.out, (const __bf16*)a.dout, a.lse, a.delta, a.nl,
                          rows);
   } else {
-    const dim3 grid((uint32_t)((rows + kPreThreads - 1) / kPreThreads));
+    // at most 2^22 workgroups (2^30 threads); they take further rows beyond that
+    const int64_t wgs = (rows * kF32Tpr + kPreThreads - 1) / kPreThreads;
+    const dim3 grid((uint32_t)(wgs < (1 << 22) ? wgs : 1 << 22));
     hipLaunchKernelGGL(bwd_pre_f32_kernel, grid, dim3(kPreThreads), 0, a.stream,
                        (const float*)a.out, (const float*)a.dout, a.lse, a.delta, a.nl, rows,
                        (int)a.d);

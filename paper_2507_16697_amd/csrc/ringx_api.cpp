@@ -333,9 +333,9 @@ ringx_status bwd_impl(const void* q, const void* k, const void* v, const void* o
   a.accumulate_dkv = accumulate_dkv != 0, a.stream = stream;
   const bool bf16 = dtype == RINGX_BF16;
   if (ringx::launch_bwd_pre(a, bf16) != hipSuccess) return RINGX_E_HIP;
-  if ((bf16 ? ringx::launch_bwd_dkdv_bf16(a) : ringx::launch_bwd_dkdv_f32(a)) != hipSuccess)
-    return RINGX_E_HIP;
-  return hip_status(bf16 ? ringx::launch_bwd_dq_bf16(a) : ringx::launch_bwd_dq_f32(a));
+  if (!bf16) return hip_status(ringx::launch_bwd_f32(a));
+  if (ringx::launch_bwd_dkdv_bf16(a) != hipSuccess) return RINGX_E_HIP;
+  return hip_status(ringx::launch_bwd_dq_bf16(a));
 }
 
 }  // namespace
@@ -581,9 +581,9 @@ ringx_status ringx_attn_bwd_step(const void* q, const void* k, const void* v, co
   a.BH = bh, a.Nq = Nq, a.Nk = Nk, a.d = d, a.R = 1, a.scale = scale, a.H = H, a.G = 1;
   a.accumulate_dkv = accumulate_dkv != 0, a.accumulate_dq = accumulate_dq != 0, a.stream = stream;
   const bool bf16 = dtype == RINGX_BF16;
-  if ((bf16 ? ringx::launch_bwd_dkdv_bf16(a) : ringx::launch_bwd_dkdv_f32(a)) != hipSuccess)
-    return RINGX_E_HIP;
-  return hip_status(bf16 ? ringx::launch_bwd_dq_bf16(a) : ringx::launch_bwd_dq_f32(a));
+  if (!bf16) return hip_status(ringx::launch_bwd_f32(a));
+  if (ringx::launch_bwd_dkdv_bf16(a) != hipSuccess) return RINGX_E_HIP;
+  return hip_status(ringx::launch_bwd_dq_bf16(a));
 }
 
 ringx_status ringx_tt_tokenize(const float* field, void* tokens, int64_t C, int64_t D, int64_t H,

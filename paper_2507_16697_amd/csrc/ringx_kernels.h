@@ -116,6 +116,7 @@ hipError_t launch_bwd_dq_bf16(const BwdArgs& a);
 hipError_t launch_bwd_dq_bf16_d64(const BwdArgs& a);   // d = 64 (bwd_dq_bf16_d64.hip)
 hipError_t launch_bwd_dkdv_f32(const BwdArgs& a);
 hipError_t launch_bwd_dq_f32(const BwdArgs& a);
+hipError_t launch_bwd_f32(const BwdArgs& a);      // both halves of the fp32 backward
 hipError_t launch_bwd_dq_ds(const DsArgs& a);   // d = 128, bf16 dS (bwd_dq_ds.hip)
 
 hipError_t launch_tt_tokenize(const TokArgs& a);
