@@ -1,7 +1,8 @@
 // Ring-chunked attention forward, bf16 storage, bf16 MFMA with fp32 accumulation (gfx950).
 //
 // One workgroup = 8 waves (two per SIMD) = one (b, h) and a tile of 256 queries (32 per wave), so
-// that each K/V tile brought into LDS serves 256 queries.  The key/value
+// that each K/V tile brought into LDS serves 256 queries; problems too small or uneven for that
+// take smaller workgroups or split the keys among a workgroup's waves (see plan()).  The key/value
 // sequence is visited as R chunks (ring steps, arXiv 2507.16697 Sec. III-A), streamed through LDS
 // in tiles of 64 keys that never straddle a chunk boundary.  K and V tiles are double buffered
 // (the on-chip analogue of the paper's ping-pong buffers) and filled by direct global->LDS loads:
@@ -38,6 +39,7 @@
 #include "ringx_device.h"
 #include "ringx_kernels.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace ringx {
@@ -47,13 +49,16 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
 constexpr float kGuard = 4294967296.0f;   // 2^32: bound on a lane's probability sum
 
-template <int D>
+// KS key streams share a workgroup's NW waves (KS = 1: all of them take every key).
+template <int D, int KS = 1, int NW = 8>
 struct FwdCfg {
-  static constexpr int kThreads = 512;
-  static constexpr int kWaves = 8;
+  static constexpr int kD = D;
+  static constexpr int kThreads = 64 * NW;
+  static constexpr int kWaves = NW;
+  static constexpr int kSW = kWaves / KS;         // waves per key stream
   static constexpr int kQW = 32;                  // queries per wave
-  static constexpr int kBQ = kWaves * kQW;        // queries per workgroup
-  static constexpr int kBK = 64;                  // keys per tile
+  static constexpr int kBQ = kSW * kQW;           // queries per workgroup
+  static constexpr int kBK = KS * D > 256 ? 32 : 64;   // keys per tile (LDS holds 4 KS tiles)
   static constexpr int kRowBytes = D * 2;
   static constexpr int kChunks = D / 8;           // 16-byte chunks per row
   static constexpr int kTileBytes = kBK * kRowBytes;   // 16 KiB (d=128), 8 KiB (d=64)
@@ -64,8 +69,14 @@ struct FwdCfg {
   // Only waves 0..3, one on each SIMD, issue the tile loads: while a wave waits for the CU's load
   // path to take its loads, the other wave of its SIMD keeps the matrix core busy (2% faster at
   // d = 128 and 5% at d = 64 than all eight waves issuing at once; two loader waves: 1% and 3%).
-  static constexpr int kLoaders = 4;
+  // With several streams the waves of each load that stream's tiles.
+  static constexpr int kLoaders = kSW < 4 ? kSW : 4;
   static constexpr int kLoads = kTileBytes / (kLoaders * 64 * 16);   // 16-byte loads per loader lane
+  static_assert(kLoads * kLoaders * 1024 == kTileBytes, "whole tiles per load round");
+  // end of the streams: 4 kCT KiB of accumulators and 512 bytes of statistics per wave of the
+  // streams after the first, in the tile buffers
+  static constexpr int kXchWave = 4 * kCT * 1024 + 512;
+  static_assert((kWaves - kSW) * kXchWave <= 4 * KS * kTileBytes, "stream exchange fits");
 };
 
 // Swizzled 16-byte chunk of (row, logical chunk c) inside a row-major tile.
@@ -82,15 +93,14 @@ __device__ __forceinline__ int tile_off(int row, int c) {   // byte offset
 
 // Per-lane byte offsets (from the tile's first row) of this lane's direct loads: 16-byte slot
 // `slot` of the swizzled tile holds logical chunk (slot % chunks) ^ swz(row) of row slot / chunks.
-template <int D>
-__device__ __forceinline__ void load_offsets(int (&goff)[FwdCfg<D>::kLoads],
-                                             int (&grow)[FwdCfg<D>::kLoads], int wave, int lane) {
-  using C = FwdCfg<D>;
+template <typename C>
+__device__ __forceinline__ void load_offsets(int (&goff)[C::kLoads], int (&grow)[C::kLoads],
+                                             int wave, int lane) {
 #pragma unroll
   for (int u = 0; u < C::kLoads; ++u) {
     const int slot = (u * C::kLoaders + (wave % C::kLoaders)) * 64 + lane;
     const int row = slot / C::kChunks;
-    const int c = (slot % C::kChunks) ^ swz<D>(row);
+    const int c = (slot % C::kChunks) ^ swz<C::kD>(row);
     grow[u] = row;
     goff[u] = row * C::kRowBytes + c * 16;
   }
@@ -99,13 +109,12 @@ __device__ __forceinline__ void load_offsets(int (&goff)[FwdCfg<D>::kLoads],
 // Issue the direct loads of one K or V tile starting at key `start` into the LDS buffer at
 // `dst`; rows at or past `hi` (only in the last tile of a chunk) are clamped to hi - 1.
 // `wdst` is the loader wave's first 1 KiB slot (wave * 1024, an SGPR).
-template <int D>
+// `wave` counts within the stream.
+template <typename C>
 __device__ __forceinline__ void issue_tile(const char* __restrict__ base, uint32_t dst,
                                            uint32_t start, uint32_t hi,
-                                           const int (&goff)[FwdCfg<D>::kLoads],
-                                           const int (&grow)[FwdCfg<D>::kLoads], int wave,
-                                           uint32_t wdst) {
-  using C = FwdCfg<D>;
+                                           const int (&goff)[C::kLoads],
+                                           const int (&grow)[C::kLoads], int wave, uint32_t wdst) {
   if (wave >= C::kLoaders) return;
   const char* src = base + (uint64_t)start * C::kRowBytes;
   if (start + C::kBK <= hi) {
@@ -123,29 +132,55 @@ __device__ __forceinline__ void issue_tile(const char* __restrict__ base, uint32
   }
 }
 
-template <int D, int MODE>
-__global__ __launch_bounds__(512, 1) void fwd_bf16_kernel(
+// One workgroup = one (b, h), kBQ queries and the chunks [rg R / RG, (rg + 1) R / RG) (RG > 1 in
+// partials mode only, where chunks are independent).  With KS > 1 key streams, stream p of the
+// workgroup takes every KS-th key tile of the range (the whole range in fused and step mode, one
+// chunk after the other in partials mode) and the streams merge through LDS at its end.
+template <int D, int MODE, int KS, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : D == 64 ? 3 : 2) void fwd_bf16_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     __bf16* __restrict__ out, float* __restrict__ lse, float* __restrict__ part_out,
     float* __restrict__ part_lse, float* __restrict__ acc_out, float* __restrict__ acc_lse,
-    int first, int BH, int H, int grp, int64_t Nq, int64_t Nk, int R, float c2) {
-  using C = FwdCfg<D>;
+    int first, int BH, int H, int grp, int64_t Nq, int64_t Nk, int R, int RG, float c2) {
+  using C = FwdCfg<D, KS, NW>;
   constexpr bool kPartials = MODE == (int)FwdMode::kPartials;
   constexpr bool kStep = MODE == (int)FwdMode::kStep;
-  __shared__ __attribute__((aligned(1024))) char lds_k[2 * C::kTileBytes];
-  __shared__ __attribute__((aligned(1024))) char lds_v[2 * C::kTileBytes];
+  constexpr bool kFused = MODE == (int)FwdMode::kFused;
+  // K buffers of every stream, then V buffers
+  __shared__ __attribute__((aligned(1024))) char lds[4 * KS * C::kTileBytes];
+  char* const lds_k = lds;
+  char* const lds_v = lds + 2 * KS * C::kTileBytes;
 
   const int t = threadIdx.x;
   const int lane = t & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wave8 = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int ks = wave8 / C::kSW;      // key stream
+  const int wave = wave8 % C::kSW;    // wave of the stream
   const int n = lane & 31;
   const int g = lane >> 5;
 
   const int64_t nqt = (Nq + C::kBQ - 1) / C::kBQ;
-  const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t bh = wg / nqt;
+  uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t q0 = (wg % nqt) * C::kBQ + wave * C::kQW;
+  wg /= nqt;
+  const int64_t bh = kPartials ? wg / RG : wg;
   if (bh >= BH) return;
+
+  const uint32_t nk = (uint32_t)Nk;
+  // this workgroup's chunks and their keys [key_lo, key_hi)
+  int r0 = 0;
+  uint32_t key_lo = 0, key_hi = nk;
+  ChunkWalk walk{nk, nk / (uint32_t)R, nk % (uint32_t)R, 0, (uint32_t)R};
+  int r_end = R;
+  if (kPartials && RG > 1) {
+    const uint32_t rg = wg % RG;
+    r0 = (int)((uint64_t)rg * R / RG);
+    r_end = (int)((uint64_t)(rg + 1) * R / RG);
+    key_lo = (uint32_t)((uint64_t)r0 * nk / R);
+    key_hi = (uint32_t)((uint64_t)r_end * nk / R);
+    walk.Nk = key_hi;
+    walk.racc = (uint32_t)((uint64_t)r0 * walk.rem % (uint32_t)R);
+  }
 
   const __bf16* qb = q + bh * Nq * D;
   const int64_t kvh = kv_head(bh, H, grp);
@@ -155,25 +190,53 @@ __global__ __launch_bounds__(512, 1) void fwd_bf16_kernel(
   const char* vb =
       static_cast<const char*>(uniform_ptr(reinterpret_cast<const char*>(v + kvh * Nk * D)));
   int goff[C::kLoads], grow[C::kLoads];
-  load_offsets<D>(goff, grow, wave, lane);
+  load_offsets<C>(goff, grow, wave, lane);
 
-  const uint32_t nk = (uint32_t)Nk;
-  ChunkWalk walk{nk, nk / (uint32_t)R, nk % (uint32_t)R, 0, (uint32_t)R};
   uint32_t wdst = (uint32_t)__builtin_amdgcn_readfirstlane(wave * 1024);
-  KeyTile t0 = walk.first();
-  KeyTile t1 = walk.next<C::kBK>(t0);
-  KeyTile t2 = walk.next<C::kBK>(t1);
-  int r0 = 0;   // chunk of t0
+  // Tiles of this wave's stream: t0 the current one, t1 and t2 the next two.  `key_end`: a tile
+  // that starts there or later does not exist.
+  KeyTile t0, t1, t2;
+  uint32_t key_end = key_hi;
+  int it = 0, nit = 0;        // KS > 1: the range's tile round and number of rounds
+  auto next_tile = [&](const KeyTile& x) -> KeyTile {
+    if constexpr (KS == 1) return walk.next<C::kBK>(x);
+    else return KeyTile{x.start + KS * C::kBK, x.hi};
+  };
 
-  // LDS byte addresses of the two K and two V buffers
-  const uint32_t lk = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_k;
-  const uint32_t lv = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_v;
+  // LDS byte addresses of the two K and two V buffers of the stream
+  const int st_off = 2 * ks * C::kTileBytes;
+  const char* const my_k = lds_k + st_off;
+  const char* const my_v = lds_v + st_off;
+  const uint32_t lk = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_k + st_off;
+  const uint32_t lv = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_v + st_off;
 
-  // K_0, V_0 and K_1 in flight while Q is loaded
-  issue_tile<D>(kb, lk, t0.start, t0.hi, goff, grow, wave, wdst);
-  issue_tile<D>(vb, lv, t0.start, t0.hi, goff, grow, wave, wdst);
-  if (t1.start < nk)
-    issue_tile<D>(kb, lk + C::kTileBytes, t1.start, t1.hi, goff, grow, wave, wdst);
+  // K_0, V_0 and K_1 of the range that starts at `lo` (KS > 1: and ends at `hi`)
+  auto start_range = [&](uint32_t lo, uint32_t hi) {
+    if constexpr (KS == 1) {
+      t0 = walk.first(lo);
+    } else {
+      key_end = hi;
+      it = 0;
+      nit = (int)(((hi - lo + C::kBK - 1) / C::kBK + KS - 1) / KS);
+      t0 = KeyTile{lo + ks * C::kBK, hi};
+    }
+    t1 = next_tile(t0);
+    t2 = next_tile(t1);
+    if (KS == 1 || t0.start < key_end) {
+      issue_tile<C>(kb, lk, t0.start, t0.hi, goff, grow, wave, wdst);
+      issue_tile<C>(vb, lv, t0.start, t0.hi, goff, grow, wave, wdst);
+    }
+    if (t1.start < key_end)
+      issue_tile<C>(kb, lk + C::kTileBytes, t1.start, t1.hi, goff, grow, wave, wdst);
+  };
+  // in flight while Q is loaded
+  if constexpr (KS > 1 && kPartials) {
+    uint32_t hi0 = key_lo + walk.q_sz;
+    if (walk.racc + walk.rem >= walk.R) ++hi0;
+    start_range(key_lo, hi0);
+  } else {
+    start_range(key_lo, key_hi);
+  }
 
   // Q fragments (B operand of S^T = K Q^T): query n of this wave, dims 16*ks + 8g .. +8.
   bf16x8 qf[C::kDSteps];
@@ -212,19 +275,73 @@ __global__ __launch_bounds__(512, 1) void fwd_bf16_kernel(
   float lc = 0.f;           // this lane's share of the chunk's row sum, relative to m2
   float lse2m = -INFINITY;  // merged log2-sum-exp over finished chunks (Eq. (5))
 
-  wait_vmem_all();
-  __syncthreads();
-
-  // S_0
   f32x16 sa[C::kKTiles], sb[C::kKTiles];
+  // S_0, once K_0 has landed
+  auto first_scores = [&] {
+    wait_vmem_all();
+    __syncthreads();
 #pragma unroll
-  for (int kt = 0; kt < C::kKTiles; ++kt) sa[kt] = f32x16{};
+    for (int kt = 0; kt < C::kKTiles; ++kt) sa[kt] = f32x16{};
 #pragma unroll
-  for (int s = 0; s < C::kDSteps; ++s)
+    for (int s = 0; s < C::kDSteps; ++s)
 #pragma unroll
-    for (int kt = 0; kt < C::kKTiles; ++kt)
-      sa[kt] = mfma32(*reinterpret_cast<const bf16x8*>(lds_k + koff[s] + kt * 32 * C::kRowBytes),
-                      qf[s], sa[kt]);
+      for (int kt = 0; kt < C::kKTiles; ++kt)
+        sa[kt] = mfma32(*reinterpret_cast<const bf16x8*>(my_k + koff[s] + kt * 32 * C::kRowBytes),
+                        qf[s], sa[kt]);
+  };
+
+  // The result of chunk r (its row sum `lrow` and log2-sum-exp `lse2r`, the accumulators as they
+  // are) where it goes: folded into the running (acc_out, acc_lse), or to the partials.
+  auto put_step = [&](float lrow, float lse2r) {
+    // Eq. (5) with the running result: out_acc <- (out_acc a + loc_out b) / (a + b)
+    const int64_t qi = q0 + n;
+    if (qi < Nq) {
+      const int64_t row = bh * Nq + qi;
+      float* ao = acc_out + row * D;
+      const float inv = 1.0f / lrow;
+      float wa = 0.f, wb = inv;
+      float lnew = lse2r;
+      if (!first) {
+        const float lold = acc_lse[row] * kLog2e;
+        const float M = fmaxf(lold, lse2r);
+        const float a = fast_exp2(lold - M);
+        const float b = fast_exp2(lse2r - M);
+        const float den = a + b;
+        wa = a / den;
+        wb = b * inv / den;
+        lnew = M + fast_log2(den);
+      }
+#pragma unroll
+      for (int c = 0; c < C::kCT; ++c)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          f32x4* dst = reinterpret_cast<f32x4*>(ao + c * 32 + 8 * rq + 4 * g);
+          const f32x4 prev = first ? f32x4{} : *dst;
+          f32x4 val;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) val[e] = prev[e] * wa + oacc[c][4 * rq + e] * wb;
+          *dst = val;
+        }
+      if (g == 0) acc_lse[row] = lnew * kLn2;
+    }
+  };
+  auto put_partial = [&](int r, float lrow, float lse2r) {
+    const int64_t qi = q0 + n;
+    if (qi < Nq) {
+      const float inv = 1.0f / lrow;
+      const int64_t row = ((int64_t)r * BH + bh) * Nq + qi;
+      float* po = part_out + row * D;
+#pragma unroll
+      for (int c = 0; c < C::kCT; ++c)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          f32x4 val = {oacc[c][4 * rq] * inv, oacc[c][4 * rq + 1] * inv,
+                       oacc[c][4 * rq + 2] * inv, oacc[c][4 * rq + 3] * inv};
+          *reinterpret_cast<f32x4*>(po + c * 32 + 8 * rq + 4 * g) = val;
+        }
+      if (g == 0) part_lse[row] = lse2r * kLn2;
+    }
+  };
 
   // One pipelined iteration for tile t0 (scores in `cur`); parity P selects the buffers: K_{j+1}
   // is read from K buffer 1-P, V_j from V buffer P; K_{j+2} lands in K buffer P, V_{j+1} in V
@@ -237,10 +354,12 @@ __global__ __launch_bounds__(512, 1) void fwd_bf16_kernel(
     // wdst counts as redefined here, so that the load slots' addresses are formed at each use
     // (scalar adds) instead of being held in registers across the loop
     asm volatile("" : "+s"(wdst));
-    if (t2.start < nk)
-      issue_tile<D>(kb, lk + P * C::kTileBytes, t2.start, t2.hi, goff, grow, wave, wdst);
-    if (t1.start < nk)
-      issue_tile<D>(vb, lv + (1 - P) * C::kTileBytes, t1.start, t1.hi, goff, grow, wave, wdst);
+    if (t2.start < key_end)
+      issue_tile<C>(kb, lk + P * C::kTileBytes, t2.start, t2.hi, goff, grow, wave, wdst);
+    if (t1.start < key_end)
+      issue_tile<C>(vb, lv + (1 - P) * C::kTileBytes, t1.start, t1.hi, goff, grow, wave, wdst);
+    // a stream's last round may hold no tile of its own
+    if (KS > 1 && t0.start >= key_end) return ++it >= nit;
     // The vector work of this half (exponentials, row sums) is the longer chain; it issues ahead
     // of the other wave's matrix products on the SIMD, which fill the gaps (priority drops again
     // for the P V half).
@@ -258,7 +377,7 @@ __global__ __launch_bounds__(512, 1) void fwd_bf16_kernel(
           if (kt * 32 + 8 * (rr >> 2) + (rr & 3) >= thr) cur[kt][rr] = -INFINITY;
     }
     // S_{j+1} = K_{j+1} Q^T on the matrix cores, P_j = exp2(t - m) on the vector ALU
-    const char* kbuf = lds_k + (1 - P) * C::kTileBytes;
+    const char* kbuf = my_k + (1 - P) * C::kTileBytes;
 #pragma unroll
     for (int kt = 0; kt < C::kKTiles; ++kt) nxt[kt] = f32x16{};
 #pragma unroll
@@ -335,7 +454,7 @@ __global__ __launch_bounds__(512, 1) void fwd_bf16_kernel(
 
     __builtin_amdgcn_s_setprio(0);
     // O += V_j^T P_j on the matrix cores
-    const char* vbuf = lds_v + P * C::kTileBytes;
+    const char* vbuf = my_v + P * C::kTileBytes;
 #pragma unroll
     for (int s = 0; s < C::kKSteps; ++s)
 #pragma unroll
@@ -354,84 +473,113 @@ __global__ __launch_bounds__(512, 1) void fwd_bf16_kernel(
     }
     __builtin_amdgcn_sched_barrier(0);
 
-    if (t0.start + C::kBK >= t0.hi) {
+    if (KS == 1 && t0.start + C::kBK >= t0.hi) {
       // end of chunk r0: loc_lse_r from the chunk's own row sum
       const float lrow = sum_halves(lc);
       const float lse2r = m2 + fast_log2(lrow);
-      if constexpr (kStep) {
-        // Eq. (5) with the running result: out_acc <- (out_acc a + loc_out b) / (a + b)
-        const int64_t qi = q0 + n;
-        if (qi < Nq) {
-          const int64_t row = bh * Nq + qi;
-          float* ao = acc_out + row * D;
-          const float inv = 1.0f / lrow;
-          float wa = 0.f, wb = inv;
-          float lnew = lse2r;
-          if (!first) {
-            const float lold = acc_lse[row] * kLog2e;
-            const float M = fmaxf(lold, lse2r);
-            const float a = fast_exp2(lold - M);
-            const float b = fast_exp2(lse2r - M);
-            const float den = a + b;
-            wa = a / den;
-            wb = b * inv / den;
-            lnew = M + fast_log2(den);
-          }
-#pragma unroll
-          for (int c = 0; c < C::kCT; ++c)
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-              f32x4* dst = reinterpret_cast<f32x4*>(ao + c * 32 + 8 * rq + 4 * g);
-              const f32x4 prev = first ? f32x4{} : *dst;
-              f32x4 val;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) val[e] = prev[e] * wa + oacc[c][4 * rq + e] * wb;
-              *dst = val;
-            }
-          if (g == 0) acc_lse[row] = lnew * kLn2;
-        }
-#pragma unroll
-        for (int c = 0; c < C::kCT; ++c) oacc[c] = f32x16{};
-        m2 = -INFINITY;
-      } else if constexpr (kPartials) {
-        const int64_t qi = q0 + n;
-        if (qi < Nq) {
-          const float inv = 1.0f / lrow;
-          const int64_t row = ((int64_t)r0 * BH + bh) * Nq + qi;
-          float* po = part_out + row * D;
-#pragma unroll
-          for (int c = 0; c < C::kCT; ++c)
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-              f32x4 val = {oacc[c][4 * rq] * inv, oacc[c][4 * rq + 1] * inv,
-                           oacc[c][4 * rq + 2] * inv, oacc[c][4 * rq + 3] * inv};
-              *reinterpret_cast<f32x4*>(po + c * 32 + 8 * rq + 4 * g) = val;
-            }
-          if (g == 0) part_lse[row] = lse2r * kLn2;
-        }
-#pragma unroll
-        for (int c = 0; c < C::kCT; ++c) oacc[c] = f32x16{};
-        m2 = -INFINITY;
-      } else {
+      if constexpr (kFused) {
         // Eq. (5) on the log-sum-exps; the numerator terms already share the reference m2
         const float M = fmaxf(lse2m, lse2r);
         lse2m = M + fast_log2(fast_exp2(lse2m - M) + fast_exp2(lse2r - M));
+      } else {
+        if constexpr (kStep) put_step(lrow, lse2r);
+        else put_partial(r0, lrow, lse2r);
+#pragma unroll
+        for (int c = 0; c < C::kCT; ++c) oacc[c] = f32x16{};
+        m2 = -INFINITY;
       }
       lc = 0.f;
       ++r0;
     }
     t0 = t1;
     t1 = t2;
-    t2 = walk.next<C::kBK>(t2);
-    return t0.start >= nk;
+    t2 = next_tile(t2);
+    if constexpr (KS == 1) return t0.start >= key_end;
+    else return ++it >= nit;
+  };
+  auto run_range = [&] {
+    first_scores();
+    while (true) {
+      if (step(sa, sb, std::integral_constant<int, 0>{})) break;
+      if (step(sb, sa, std::integral_constant<int, 1>{})) break;
+    }
   };
 
-  while (true) {
-    if (step(sa, sb, std::integral_constant<int, 0>{})) break;
-    if (step(sb, sa, std::integral_constant<int, 1>{})) break;
+  if constexpr (KS == 1) {
+    run_range();
+  } else {
+    while (true) {
+      const uint32_t hi = key_end;
+      run_range();
+      // The streams' (m, l, O) of this range through LDS into stream 0, in stream order.  Every
+      // wave is past its last tile read once all have met here.
+      __syncthreads();
+      char* const xch = lds;
+      float lrow = sum_halves(lc);
+      if (ks > 0) {
+        char* mine = xch + ((ks - 1) * C::kSW + wave) * C::kXchWave;
+#pragma unroll
+        for (int c = 0; c < C::kCT; ++c)
+#pragma unroll
+          for (int rq = 0; rq < 4; ++rq)
+            *reinterpret_cast<f32x4*>(mine + (c * 4 + rq) * 1024 + lane * 16) =
+                f32x4{oacc[c][4 * rq], oacc[c][4 * rq + 1], oacc[c][4 * rq + 2],
+                      oacc[c][4 * rq + 3]};
+        *reinterpret_cast<f32x2*>(mine + C::kCT * 4096 + lane * 8) = f32x2{m2, lrow};
+      }
+      __syncthreads();
+      if (ks == 0) {
+        const char* const others = xch + wave * C::kXchWave;
+        float M = m2;
+        f32x2 st[KS - 1];
+#pragma unroll
+        for (int p = 0; p < KS - 1; ++p) {
+          st[p] = *reinterpret_cast<const f32x2*>(others + p * C::kSW * C::kXchWave +
+                                                  C::kCT * 4096 + lane * 8);
+          M = fmaxf(M, st[p][0]);
+        }
+        const float w0 = fast_exp2(m2 - M);
+        lrow *= w0;
+#pragma unroll
+        for (int c = 0; c < C::kCT; ++c) oacc[c] *= w0;
+#pragma unroll
+        for (int p = 0; p < KS - 1; ++p) {
+          const float w = fast_exp2(st[p][0] - M);
+          lrow = __builtin_fmaf(w, st[p][1], lrow);
+#pragma unroll
+          for (int c = 0; c < C::kCT; ++c)
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+              const f32x4 x = *reinterpret_cast<const f32x4*>(
+                  others + p * C::kSW * C::kXchWave + (c * 4 + rq) * 1024 + lane * 16);
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                oacc[c][4 * rq + e] = __builtin_fmaf(w, x[e], oacc[c][4 * rq + e]);
+            }
+        }
+        const float lse2r = M + fast_log2(lrow);
+        if constexpr (kFused) {
+          m2 = M;
+          lse2m = lse2r;
+        } else if constexpr (kStep) {
+          put_step(lrow, lse2r);
+        } else {
+          put_partial(r0, lrow, lse2r);
+        }
+      }
+      if constexpr (!kPartials) break;
+      // the next chunk of this workgroup
+      if (++r0 >= r_end) break;
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < C::kCT; ++c) oacc[c] = f32x16{};
+      m2 = -INFINITY;
+      lc = 0.f;
+      start_range(hi, (uint32_t)((uint64_t)(r0 + 1) * nk / R));
+    }
   }
 
-  if constexpr (MODE == (int)FwdMode::kFused) {
+  if (kFused && ks == 0) {
     const int64_t qi = q0 + n;
     if (qi < Nq) {
       // out = numerator / Eq. (5) denominator = oacc * 2^(m - lse)
@@ -451,25 +599,66 @@ __global__ __launch_bounds__(512, 1) void fwd_bf16_kernel(
   }
 }
 
-template <int D, int MODE>
-hipError_t launch(const FwdArgs& a) {
-  using C = FwdCfg<D>;
-  const int64_t nqt = (a.Nq + C::kBQ - 1) / C::kBQ;
-  const int64_t nwg = nqt * a.BH;
-  hipLaunchKernelGGL((fwd_bf16_kernel<D, MODE>), dim3((uint32_t)nwg), dim3(C::kThreads), 0,
+template <int D, int MODE, int KS, int NW>
+hipError_t launch(const FwdArgs& a, int64_t RG) {
+  using C = FwdCfg<D, KS, NW>;
+  const int64_t nwg = (a.Nq + C::kBQ - 1) / C::kBQ * a.BH * RG;
+  hipLaunchKernelGGL((fwd_bf16_kernel<D, MODE, KS, NW>), dim3((uint32_t)nwg), dim3(C::kThreads), 0,
                      a.stream, (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v,
                      (__bf16*)a.out, a.lse, a.part_out, a.part_lse, a.acc_out, a.acc_lse,
-                     a.first ? 1 : 0, (int)a.BH, (int)a.H, (int)a.G, a.Nq, a.Nk, (int)a.R,
+                     a.first ? 1 : 0, (int)a.BH, (int)a.H, (int)a.G, a.Nq, a.Nk, (int)a.R, (int)RG,
                      a.scale * kLog2e);
   return hipGetLastError();
+}
+
+// How a launch is cut.  A CU runs one 8-wave workgroup (256 queries) at a time, so n of them take
+// ceil(n / 256) rounds, and with few of them, or few in the last round, most of the chip is idle.
+struct FwdPlan {
+  int ks = 1;       // key streams per workgroup
+  bool half = false;   // 4-wave workgroups of 128 queries, two (d = 128) or three (d = 64) per CU
+  int64_t rg = 1;   // chunk groups (partials)
+};
+
+FwdPlan plan(const FwdArgs& a, bool partials) {
+  FwdPlan p;
+  int64_t n = (a.Nq + 255) / 256 * a.BH;
+  // Partials: chunks are independent, so they are spread over workgroups until there are four
+  // rounds (Nq = 2048, 8 chunks of 4096, 16 heads, d = 128: 664 -> 453 us).
+  if (partials)
+    while (p.rg < a.R && n * p.rg < 1024) p.rg = std::min<int64_t>(2 * p.rg, a.R);
+  n *= p.rg;
+  // One round even with 64- or 128-query workgroups whose waves split the keys four or two ways.
+  // At 64 workgroups of 256 queries, 4096 keys: d = 128 88 us whole, 54 two ways, 45 four ways;
+  // d = 64 66, 40 and 28.  Past one round splitting loses (128: 71 two ways, 85 four ways; 192:
+  // 105 whole, 120 two ways), because a tile then serves fewer queries.  Partials, which split over
+  // chunks already, take two ways at most.
+  if (n <= 64 && !partials) p.ks = 4;
+  else if (n <= 128) p.ks = 2;
+  while (p.ks > 1 && a.Nk / p.rg < 64 * p.ks) p.ks /= 2;
+  // A last round at most half full costs as much as a full one; workgroups of half the size end
+  // closer together (320: d = 64 140 -> 108 us at 4096 keys, d = 128 209 -> 188; 384: 139 -> 116,
+  // 205 -> 197), but read every tile for half the queries, which is 2-3% slower where the rounds
+  // are full and gains nothing past a few of them (640: 215 -> 187, 334 -> 326; 1024: even).
+  p.half = n > 256 && n < 1024 && (n - 1) % 256 < 128;
+  return p;
+}
+
+template <int D, int MODE>
+hipError_t launch_plan(const FwdArgs& a) {
+  const FwdPlan p = plan(a, MODE == (int)FwdMode::kPartials);
+  if (p.half) return launch<D, MODE, 1, 4>(a, p.rg);
+  if constexpr (MODE != (int)FwdMode::kPartials)
+    if (p.ks == 4) return launch<D, MODE, 4, 8>(a, p.rg);
+  if (p.ks == 2) return launch<D, MODE, 2, 8>(a, p.rg);
+  return launch<D, MODE, 1, 8>(a, p.rg);
 }
 
 template <int D>
 hipError_t launch_mode(const FwdArgs& a, FwdMode mode) {
   switch (mode) {
-    case FwdMode::kPartials: return launch<D, (int)FwdMode::kPartials>(a);
-    case FwdMode::kStep: return launch<D, (int)FwdMode::kStep>(a);
-    default: return launch<D, (int)FwdMode::kFused>(a);
+    case FwdMode::kPartials: return launch_plan<D, (int)FwdMode::kPartials>(a);
+    case FwdMode::kStep: return launch_plan<D, (int)FwdMode::kStep>(a);
+    default: return launch_plan<D, (int)FwdMode::kFused>(a);
   }
 }
 

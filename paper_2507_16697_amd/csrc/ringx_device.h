@@ -64,10 +64,16 @@ struct ChunkWalk {
   uint32_t Nk, q_sz, rem, racc;   // Nk, Nk / R, Nk mod R, running remainder
   uint32_t R;
   __device__ KeyTile first() {
-    racc = rem;
+    racc = 0;
+    return first(0);
+  }
+  // the first tile of the chunk that starts at `lo`, with racc = (chunk index * rem) mod R; the walk
+  // ends where the chunk that ends at Nk does
+  __device__ KeyTile first(uint32_t lo) {
+    racc += rem;
     const uint32_t extra = racc >= R ? 1u : 0u;
     racc -= extra * R;
-    return {0, q_sz + extra};
+    return {lo, lo + q_sz + extra};
   }
   template <int BK>
   __device__ KeyTile next(const KeyTile& t) {
