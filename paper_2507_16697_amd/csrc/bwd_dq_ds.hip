@@ -248,12 +248,213 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_ds_kernel(
   }
 }
 
+// The same product for slabs with few query groups: one workgroup = 4 waves = one query head and 32
+// queries, each wave a key stream of its own (every fourth 32-key block), so that a slab has four
+// times as many workgroups and every CU four independent streams.  A wave's 2 KiB of dS and 8 KiB
+// of K rows per block go through its own four-stage LDS ring, three blocks ahead, with no barrier
+// in the loop (30 KiB per wave in flight; the load path of a CU moves 64 bytes per clock, which
+// bounds this kernel: K is read once per 32 queries instead of 128).  The streams' dQ^T meet in LDS
+// at the end, a quarter of the head dims per wave, added in stream order.
+struct DqsStream {
+  static constexpr int kBK = 32;
+  static constexpr int kStage = 10240;             // dS unit, then K rows
+  static constexpr int kStages = 4;
+  static constexpr int kWave = kStages * kStage;
+  static constexpr int kLoads = 10;                // vector-memory operations per block
+};
+
+__global__ __launch_bounds__(256, 1) void bwd_dq_ds_stream_kernel(
+    const char* __restrict__ ds, const __bf16* __restrict__ k, float* __restrict__ dq, int nh,
+    int grp, int64_t Nq, int64_t Nk, int R, int tpc, float neg_scale) {
+  using C = DqsCfg;
+  using T = DqsStream;
+  constexpr int D = C::D;
+  __shared__ __attribute__((aligned(1024))) char lds[4 * T::kWave];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 31;
+  const int g = lane >> 5;
+  char* const ring = lds + wave * T::kWave;
+  const uint32_t lbase = (uint32_t)__builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds + wave * T::kWave);
+
+  const int64_t nqb = (Nq + 31) / 32, nqg = (Nq + C::kBQ - 1) / C::kBQ;
+  const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t j = wg / nqb;          // query head within the slab
+  const int64_t qb = wg % nqb;         // 32-query block
+  if (j >= nh) return;
+  const int64_t nkb = 4 * (int64_t)R * tpc;
+  const char* kbase = static_cast<const char*>(
+      uniform_ptr(reinterpret_cast<const char*>(k + (j / grp) * Nk * D)));
+  const char* dsbase = static_cast<const char*>(
+      uniform_ptr(ds + ds_unit_offset(j, qb >> 2, 0, qb & 3, nqg, nkb)));
+  const int64_t kbstride = nqg * 4 * kDsUnitBytes;   // bytes from one key block to the next
+
+  // the 32-key blocks of every chunk in order; this wave takes blocks wave, wave + 4, ...
+  int total = 0;
+  for (int r = 0; r < R; ++r) {
+    const int64_t lo = (int64_t)r * Nk / R, hi = (int64_t)(r + 1) * Nk / R;
+    total += (int)((hi - lo + T::kBK - 1) / T::kBK);
+  }
+  const int cnt = (total - wave + 3) / 4;
+  const uint32_t nk = (uint32_t)Nk;
+  struct Walk {
+    ChunkWalk w;
+    KeyTile t;
+    int r, kb;                         // chunk, key block of the padded key axis
+    __device__ void next(int steps, int tpc4) {
+      for (int i = 0; i < steps; ++i) {
+        if (t.start + T::kBK < t.hi) {
+          ++kb;
+        } else {
+          ++r;
+          kb = r * tpc4;
+        }
+        t = w.next<T::kBK>(t);
+      }
+    }
+  };
+  Walk ld{ChunkWalk{nk, nk / (uint32_t)R, nk % (uint32_t)R, 0, (uint32_t)R}, KeyTile{}, 0, 0};
+  ld.t = ld.w.first();
+  ld.next(wave, 4 * tpc);
+  Walk cu = ld;
+
+  // lane offsets of the loads: dS chunk ds_pos(64 u + lane) of the unit; K row 4 u + lane / 16 at a
+  // swizzled chunk (the swizzle of round u is that of round u % 4)
+  uint32_t doffs[2], koffs[4];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) doffs[u] = (uint32_t)ds_pos(64 * u + lane) * 16;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int row = 4 * u + (lane >> 4);
+    koffs[u] = (uint32_t)(row * C::kRowBytes + (((lane & 15) ^ swz(row)) << 4));
+  }
+  auto issue_next = [&](int stage) {
+    const uint32_t dst = lbase + stage * T::kStage;
+    const char* dt = dsbase + (int64_t)ld.kb * kbstride;
+    const char* kt = kbase + (uint64_t)ld.t.start * C::kRowBytes;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) load_lds16_s(dt, doffs[u], dst + u * 1024);
+    if (ld.t.start + T::kBK <= ld.t.hi) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        load_lds16_s(kt + (u >> 2) * 4096, koffs[u & 3], dst + kDsUnitBytes + u * 1024);
+    } else {
+      // rows past the chunk's end are clamped to its last key (and zeroed once landed)
+      cold_path();
+      const int last = (int)(ld.t.hi - 1 - ld.t.start);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int row = 4 * u + (lane >> 4);
+        const uint32_t off = koffs[u & 3] + (u >> 2) * 4096 -
+                             (row > last ? (row - last) * C::kRowBytes : 0);
+        load_lds16_s(kt, off, dst + kDsUnitBytes + u * 1024);
+      }
+    }
+    ld.next(4, 4 * tpc);
+  };
+#pragma unroll
+  for (int s = 0; s < T::kStages - 1; ++s)
+    if (s < cnt) issue_next(s);
+
+  // transposed-read offsets, as in the kernel above (the unit is this wave's only one)
+  int toff[2][C::kCT], doff[2];
+  {
+    const int G = lane >> 4;
+    const int rr = (lane & 15) >> 2, p = lane & 3;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int c = 0; c < C::kCT; ++c) {
+        const int row = 4 * g + 8 * h + rr;
+        const int col = 32 * c + 16 * (G & 1) + 4 * p;
+        toff[h][c] = tile_off(row, col >> 3) + (col & 7) * 2;
+      }
+      doff[h] = ds_pos(64 * (G & 1) + 32 * (p >> 1) + 4 * (G >> 1) + 8 * h + rr) * 16 + 8 * (p & 1);
+    }
+  }
+  f32x16 acc[C::kCT];
+#pragma unroll
+  for (int c = 0; c < C::kCT; ++c) acc[c] = f32x16{};
+
+  for (int it = 0; it < cnt; ++it) {
+    char* const st = ring + (it % T::kStages) * T::kStage;
+    // block it landed (the next two may stay in flight); this wave's reads of block it-1, whose
+    // stage the next load overwrites, are done
+    if (it + T::kStages - 2 < cnt)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((T::kStages - 2) * T::kLoads) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    if (it + T::kStages - 1 < cnt) issue_next((it + T::kStages - 1) % T::kStages);
+    char* const kl = st + kDsUnitBytes;
+    const int valid = (int)min<uint32_t>(T::kBK, cu.t.hi - cu.t.start);
+    if (valid < T::kBK) {
+      // rows valid .. 31 belong to no key (a wave's LDS operations stay in order)
+      cold_path();
+      for (int i = lane; i < (T::kBK - valid) * C::kChunks; i += 64)
+        *reinterpret_cast<u32x4*>(kl + (valid + i / C::kChunks) * C::kRowBytes +
+                                  (i % C::kChunks) * 16) = u32x4{};
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    cu.next(4, 4 * tpc);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const char* db = st + s * 256;
+      const bf16x4 b0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(db + doff[0]));
+      const bf16x4 b1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(db + doff[1]));
+      const bf16x8 bop = __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
+      const char* kb = kl + 16 * s * C::kRowBytes;
+#pragma unroll
+      for (int c = 0; c < C::kCT; ++c) {
+        const bf16x4 a0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(kb + toff[0][c]));
+        const bf16x4 a1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(kb + toff[1][c]));
+        acc[c] = mfma32(__builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7), bop, acc[c]);
+      }
+    }
+  }
+
+  // wave w adds the four streams' head dims 32 w .. 32 w + 31
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < C::kCT; ++c)
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq)
+      *reinterpret_cast<f32x4*>(lds + ((wave * C::kCT + c) * 4 + rq) * 1024 + lane * 16) =
+          f32x4{acc[c][4 * rq], acc[c][4 * rq + 1], acc[c][4 * rq + 2], acc[c][4 * rq + 3]};
+  __syncthreads();
+  static_assert(C::kCT == 4, "one 32-dim block per wave");
+  const int qn = 16 * (n >> 4) + 4 * ((n >> 3) & 1) + 8 * ((n >> 2) & 1) + (n & 3);
+  const int64_t qi = qb * 32 + qn;
+  if (qi < Nq) {
+    float* row = dq + (j * Nq + qi) * D;
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) {
+      f32x4 x = {};
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        x += *reinterpret_cast<const f32x4*>(lds + ((p * C::kCT + wave) * 4 + rq) * 1024 +
+                                             lane * 16);
+      *reinterpret_cast<f32x4*>(row + 32 * wave + 8 * rq + 4 * g) = x * neg_scale;
+    }
+  }
+}
+
 }  // namespace
 
 hipError_t launch_bwd_dq_ds(const DsArgs& a) {
   using C = DqsCfg;
   const int64_t nqg = (a.Nq + C::kBQ - 1) / C::kBQ;
   const int64_t nwg = a.nh * nqg;
+  // Up to 128 query groups, which leave half of the chip's CUs without work and the others with one
+  // workgroup to hide its own loads: 64 groups x 16384 keys 191 -> 90 us, 128 groups 236 -> 176,
+  // 192 groups even, 256 groups 305 against 341.
+  if (nwg <= 128) {
+    const int64_t nsw = a.nh * ((a.Nq + 31) / 32);
+    hipLaunchKernelGGL(bwd_dq_ds_stream_kernel, dim3((uint32_t)nsw), dim3(256), 0, a.stream,
+                       static_cast<const char*>(a.ds), static_cast<const __bf16*>(a.k), a.dq,
+                       (int)a.nh, (int)a.G, a.Nq, a.Nk, (int)a.R, (int)a.tpc, -a.scale);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(bwd_dq_ds_kernel, dim3((uint32_t)nwg), dim3(C::kThreads), 0, a.stream,
                      static_cast<const char*>(a.ds), static_cast<const __bf16*>(a.k), a.dq,
                      (int)a.nh, (int)a.G, a.Nq, a.Nk, (int)a.R, (int)a.tpc, -a.scale);
