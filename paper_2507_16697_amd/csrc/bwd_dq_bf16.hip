@@ -1,5 +1,6 @@
 // Recompute backward of ring-chunked attention, dQ part at head size 128: bf16 MFMA with fp32
-// accumulation (gfx950).  Head size 64 runs the two-waves-per-SIMD kernel in bwd_dq_bf16_d64.hip.
+// accumulation (gfx950).  Head size 64, and launches that have to be cut into smaller workgroups,
+// run the two-waves-per-SIMD kernel in bwd_dq_bf16_d64.hip.
 //
 // Query-stationary, like the forward: one workgroup = 4 waves (one per SIMD) = one (b, h) and 256
 // queries, 64 per wave as two 32-query blocks.  The key/value sequence is streamed chunk by chunk
@@ -418,8 +419,9 @@ hipError_t launch(const BwdArgs& a) {
 }  // namespace
 
 hipError_t launch_bwd_dq_bf16(const BwdArgs& a) {
-  if (a.d == 128) return launch<128>(a);
-  return launch_bwd_dq_bf16_d64(a);
+  const QueryCut c = query_cut((a.Nq + 255) / 256 * a.BH, a.Nk);
+  if (a.d == 128 && c.ks == 1 && !c.half) return launch<128>(a);
+  return launch_bwd_dq_bf16_two_waves(a, c);
 }
 
 }  // namespace ringx

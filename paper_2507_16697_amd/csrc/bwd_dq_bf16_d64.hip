@@ -2,6 +2,8 @@
 // accumulation (gfx950).  At d = 64 a score element carries more vector work per matrix product
 // than one wave can hide behind its own products, so this kernel runs two waves per SIMD (the
 // d = 128 kernel in bwd_dq_bf16.hip runs one wave per SIMD on a fixed software-pipelined schedule).
+// Where the launch has to be cut smaller (query_cut in ringx_kernels.h) this kernel also serves
+// d = 128, whose one-wave schedule has no room for a second key stream in LDS.
 //
 // Query-stationary, like the forward: one workgroup = 8 waves = one (b, h) and 256 queries (32
 // per wave).  The key/value sequence is streamed chunk by chunk (ring steps, arXiv 2507.16697
@@ -24,13 +26,16 @@ namespace {
 
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-template <int D>
+// KS key streams share a workgroup's NW waves (KS = 1: all of them take every tile).
+template <int D, int KS, int NW>
 struct DqCfg {
-  static constexpr int kThreads = 512;
-  static constexpr int kWaves = 8;
+  static constexpr int kD = D;
+  static constexpr int kThreads = 64 * NW;
+  static constexpr int kWaves = NW;
+  static constexpr int kSW = kWaves / KS;          // waves per key stream
   static constexpr int kQW = 32;
-  static constexpr int kBQ = kWaves * kQW;
-  static constexpr int kBK = 64;                   // keys per tile
+  static constexpr int kBQ = kSW * kQW;
+  static constexpr int kBK = KS * D > 256 ? 32 : 64;   // keys per tile (LDS holds 4 KS tiles)
   static constexpr int kRowBytes = D * 2;
   static constexpr int kChunks = D / 8;
   static constexpr int kTileBytes = kBK * kRowBytes;
@@ -38,7 +43,9 @@ struct DqCfg {
   static constexpr int kDSteps = D / 16;
   static constexpr int kKSteps = kBK / 16;
   static constexpr int kCT = D / 32;
-  static constexpr int kLoads = kTileBytes / (kThreads * 16);
+  static constexpr int kLoads = kTileBytes / (kSW * 64 * 16);   // by the waves of the stream
+  static constexpr int kXchWave = 4 * kCT * 1024;               // one wave's dQ^T accumulators
+  static_assert((kWaves - kSW) * kXchWave <= 4 * KS * kTileBytes, "stream exchange fits");
 };
 
 template <int D>
@@ -51,36 +58,35 @@ __device__ __forceinline__ int tile_off(int row, int c) {
   return row * (D * 2) + ((c ^ swz<D>(row)) << 4);
 }
 
-template <int D>
-__device__ __forceinline__ void load_offsets(int (&goff)[DqCfg<D>::kLoads],
-                                             int (&grow)[DqCfg<D>::kLoads], int wave, int lane) {
-  using C = DqCfg<D>;
+template <typename C>
+__device__ __forceinline__ void load_offsets(int (&goff)[C::kLoads], int (&grow)[C::kLoads],
+                                             int wave, int lane) {
 #pragma unroll
   for (int u = 0; u < C::kLoads; ++u) {
-    const int slot = (u * C::kWaves + wave) * 64 + lane;
+    const int slot = (u * C::kSW + wave) * 64 + lane;
     const int row = slot / C::kChunks;
-    const int c = (slot % C::kChunks) ^ swz<D>(row);
+    const int c = (slot % C::kChunks) ^ swz<C::kD>(row);
     grow[u] = row;
     goff[u] = row * C::kRowBytes + c * 16;
   }
 }
 
 // Direct loads of one K/V tile starting at key `start`; rows at or past `hi` (only in the last
-// tile of a chunk) are clamped to hi - 1.  Scalar tile bases plus 32-bit lane offsets.
-template <int D>
+// tile of a chunk) are clamped to hi - 1.  Scalar tile bases plus 32-bit lane offsets.  `wave`
+// counts within the stream.
+template <typename C>
 __device__ __forceinline__ void issue_tile(const char* __restrict__ kb,
                                            const char* __restrict__ vb, uint32_t kdst,
                                            uint32_t vdst, uint32_t start, uint32_t hi,
-                                           const int (&goff)[DqCfg<D>::kLoads],
-                                           const int (&grow)[DqCfg<D>::kLoads], int wave) {
-  using C = DqCfg<D>;
+                                           const int (&goff)[C::kLoads],
+                                           const int (&grow)[C::kLoads], int wave) {
   const char* kt = kb + (uint64_t)start * C::kRowBytes;
   const char* vt = vb + (uint64_t)start * C::kRowBytes;
   if (start + C::kBK <= hi) {
 #pragma unroll
     for (int u = 0; u < C::kLoads; ++u) {
       const uint32_t wbase =
-          (uint32_t)__builtin_amdgcn_readfirstlane((u * C::kWaves + wave) * 1024);
+          (uint32_t)__builtin_amdgcn_readfirstlane((u * C::kSW + wave) * 1024);
       load_lds16_s(kt, (uint32_t)goff[u], kdst + wbase);
       load_lds16_s(vt, (uint32_t)goff[u], vdst + wbase);
     }
@@ -91,26 +97,32 @@ __device__ __forceinline__ void issue_tile(const char* __restrict__ kb,
     for (int u = 0; u < C::kLoads; ++u) {
       const int off = grow[u] <= last ? goff[u] : goff[u] - (grow[u] - last) * C::kRowBytes;
       const uint32_t wbase =
-          (uint32_t)__builtin_amdgcn_readfirstlane((u * C::kWaves + wave) * 1024);
+          (uint32_t)__builtin_amdgcn_readfirstlane((u * C::kSW + wave) * 1024);
       load_lds16_s(kt, (uint32_t)off, kdst + wbase);
       load_lds16_s(vt, (uint32_t)off, vdst + wbase);
     }
   }
 }
 
-template <int D>
-__global__ __launch_bounds__(512, 1) void bwd_dq_kernel(
+// With KS > 1 key streams, stream p of the workgroup takes every KS-th key tile, and the streams'
+// dQ^T meet in LDS at the end.
+template <int D, int KS, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dq_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ lse,
     const float* __restrict__ delta, float* __restrict__ dq, int BH, int H, int grp, int64_t Nq,
     int64_t Nk, int R, float c2, float scale, int accumulate) {
-  using C = DqCfg<D>;
-  __shared__ __attribute__((aligned(1024))) char lds_k[2 * C::kTileBytes];
-  __shared__ __attribute__((aligned(1024))) char lds_v[2 * C::kTileBytes];
+  using C = DqCfg<D, KS, NW>;
+  // per stream two K buffers, then two V buffers
+  __shared__ __attribute__((aligned(1024))) char lds[4 * KS * C::kTileBytes];
 
   const int t = threadIdx.x;
   const int lane = t & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wave8 = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int ks = wave8 / C::kSW;      // key stream
+  const int wave = wave8 % C::kSW;    // wave of the stream
+  const char* const lds_k = lds + 4 * ks * C::kTileBytes;
+  const char* const lds_v = lds_k + 2 * C::kTileBytes;
   const int n = lane & 31;
   const int g = lane >> 5;
 
@@ -126,16 +138,26 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_kernel(
   const char* vb =
       static_cast<const char*>(uniform_ptr(reinterpret_cast<const char*>(v + kvh * Nk * D)));
   int goff[C::kLoads], grow[C::kLoads];
-  load_offsets<D>(goff, grow, wave, lane);
+  load_offsets<C>(goff, grow, wave, lane);
 
   // the chunked key sequence, one tile at a time (32-bit positions, no divisions)
   const uint32_t nk = (uint32_t)Nk;
   ChunkWalk walk{nk, nk / (uint32_t)R, nk % (uint32_t)R, 0, (uint32_t)R};
   KeyTile ct = walk.first();
+  // KS > 1: rounds of KS tiles (a chunk has ceil(len / kBK) tiles, len = Nk / R or, in Nk mod R of
+  // them, one more); a stream's last round may be empty
+  int rounds = 0;
+  if constexpr (KS > 1) {
+    const uint32_t c0 = (walk.q_sz + C::kBK - 1) / C::kBK, c1 = walk.q_sz / C::kBK + 1;
+    rounds = (int)(((uint64_t)R * c0 + (uint64_t)walk.rem * (c1 - c0) + KS - 1) / KS);
+    for (int i = 0; i < ks; ++i) ct = walk.next<C::kBK>(ct);
+  }
 
-  const uint32_t lk = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_k;
-  const uint32_t lv = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_v;
-  issue_tile<D>(kb, vb, lk, lv, ct.start, ct.hi, goff, grow, wave);
+  const uint32_t lk = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds +
+                      4 * ks * C::kTileBytes;
+  const uint32_t lv = lk + 2 * C::kTileBytes;
+  if (KS == 1 || ct.start < nk)
+    issue_tile<C>(kb, vb, lk, lv, ct.start, ct.hi, goff, grow, wave);
 
   // this lane's query: Q and dO fragments (B operands), -lse*log2e and D
   int64_t qi = q0 + n;
@@ -195,11 +217,15 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_kernel(
   wait_vmem_all();
   __syncthreads();
 
-  while (true) {
-    const KeyTile nt = walk.next<C::kBK>(ct);
+  auto tile = [&] {
+    KeyTile nt = walk.next<C::kBK>(ct);
+    if constexpr (KS > 1) {
+#pragma unroll
+      for (int i = 1; i < KS; ++i) nt = walk.next<C::kBK>(nt);
+    }
     const bool has_next = nt.start < nk;
     if (has_next)
-      issue_tile<D>(kb, vb, lk + (cur ^ 1) * C::kTileBytes, lv + (cur ^ 1) * C::kTileBytes,
+      issue_tile<C>(kb, vb, lk + (cur ^ 1) * C::kTileBytes, lv + (cur ^ 1) * C::kTileBytes,
                     nt.start, nt.hi, goff, grow, wave);
 
     const char* kbuf = lds_k;   // koff and toff hold the buffer
@@ -270,17 +296,52 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_kernel(
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
     }
 
-    if (!has_next) break;
+    ct = nt;
+    return has_next;
+  };
+  auto swap_buffers = [&] {
     wait_vmem_all();
     __syncthreads();
     cur ^= 1;
-    ct = nt;
 #pragma unroll
     for (int s = 0; s < C::kDSteps; ++s) koff[s] ^= C::kTileBytes;
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int c = 0; c < C::kCT; ++c) toff[h][c] ^= C::kTileBytes;
+  };
+  if constexpr (KS == 1) {
+    while (tile()) swap_buffers();
+  } else {
+    for (int it = 0; it < rounds; ++it) {
+      if (it > 0) swap_buffers();
+      if (ct.start < nk) tile();
+    }
+    // the streams' accumulators into stream 0, in stream order, once every tile has been read
+    __syncthreads();
+    char* const xch = lds + wave * C::kXchWave + lane * 16;
+    if (ks > 0) {
+#pragma unroll
+      for (int c = 0; c < C::kCT; ++c)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq)
+          *reinterpret_cast<f32x4*>(xch + (ks - 1) * C::kSW * C::kXchWave + (c * 4 + rq) * 1024) =
+              f32x4{dqacc[c][4 * rq], dqacc[c][4 * rq + 1], dqacc[c][4 * rq + 2],
+                    dqacc[c][4 * rq + 3]};
+    }
+    __syncthreads();
+    if (ks > 0) return;
+#pragma unroll
+    for (int p = 0; p < KS - 1; ++p)
+#pragma unroll
+      for (int c = 0; c < C::kCT; ++c)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(xch + p * C::kSW * C::kXchWave +
+                                                          (c * 4 + rq) * 1024);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dqacc[c][4 * rq + e] += x[e];
+        }
   }
 
   if (q_ok) {
@@ -298,21 +359,29 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_kernel(
   }
 }
 
-template <int D>
+template <int D, int KS, int NW>
 hipError_t launch(const BwdArgs& a) {
-  using C = DqCfg<D>;
+  using C = DqCfg<D, KS, NW>;
   const int64_t nqt = (a.Nq + C::kBQ - 1) / C::kBQ;
   const int64_t nwg = nqt * a.BH;
-  hipLaunchKernelGGL((bwd_dq_kernel<D>), dim3((uint32_t)nwg), dim3(C::kThreads), 0, a.stream,
-                     (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v,
+  hipLaunchKernelGGL((bwd_dq_kernel<D, KS, NW>), dim3((uint32_t)nwg), dim3(C::kThreads), 0,
+                     a.stream, (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v,
                      (const __bf16*)a.dout, a.lse, a.delta, a.dq, (int)a.BH, (int)a.H, (int)a.G,
-                     a.Nq, a.Nk,
-                     (int)a.R, a.scale * kLog2e, a.scale, a.accumulate_dq ? 1 : 0);
+                     a.Nq, a.Nk, (int)a.R, a.scale * kLog2e, a.scale, a.accumulate_dq ? 1 : 0);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_bwd_dq_bf16_d64(const BwdArgs& a) { return launch<64>(a); }
+hipError_t launch_bwd_dq_bf16_two_waves(const BwdArgs& a, const QueryCut& c) {
+  if (a.d == 128) {
+    if (c.half) return launch<128, 1, 4>(a);
+    return c.ks == 4 ? launch<128, 4, 8>(a) : launch<128, 2, 8>(a);
+  }
+  if (c.half) return launch<64, 1, 4>(a);
+  if (c.ks == 4) return launch<64, 4, 8>(a);
+  if (c.ks == 2) return launch<64, 2, 8>(a);
+  return launch<64, 1, 8>(a);
+}
 
 }  // namespace ringx

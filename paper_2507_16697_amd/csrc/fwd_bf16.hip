@@ -2,7 +2,7 @@
 //
 // One workgroup = 8 waves (two per SIMD) = one (b, h) and a tile of 256 queries (32 per wave), so
 // that each K/V tile brought into LDS serves 256 queries; problems too small or uneven for that
-// take smaller workgroups or split the keys among a workgroup's waves (see plan()).  The key/value
+// take smaller workgroups or split the keys among a workgroup's waves (query_cut in ringx_kernels.h).  The key/value
 // sequence is visited as R chunks (ring steps, arXiv 2507.16697 Sec. III-A), streamed through LDS
 // in tiles of 64 keys that never straddle a chunk boundary.  K and V tiles are double buffered
 // (the on-chip analogue of the paper's ping-pong buffers) and filled by direct global->LDS loads:
@@ -611,45 +611,32 @@ hipError_t launch(const FwdArgs& a, int64_t RG) {
   return hipGetLastError();
 }
 
-// How a launch is cut.  A CU runs one 8-wave workgroup (256 queries) at a time, so n of them take
-// ceil(n / 256) rounds, and with few of them, or few in the last round, most of the chip is idle.
 struct FwdPlan {
-  int ks = 1;       // key streams per workgroup
-  bool half = false;   // 4-wave workgroups of 128 queries, two (d = 128) or three (d = 64) per CU
+  QueryCut cut;
   int64_t rg = 1;   // chunk groups (partials)
 };
 
 FwdPlan plan(const FwdArgs& a, bool partials) {
   FwdPlan p;
-  int64_t n = (a.Nq + 255) / 256 * a.BH;
+  const int64_t n = (a.Nq + 255) / 256 * a.BH;
   // Partials: chunks are independent, so they are spread over workgroups until there are four
   // rounds (Nq = 2048, 8 chunks of 4096, 16 heads, d = 128: 664 -> 453 us).
   if (partials)
     while (p.rg < a.R && n * p.rg < 1024) p.rg = std::min<int64_t>(2 * p.rg, a.R);
-  n *= p.rg;
-  // One round even with 64- or 128-query workgroups whose waves split the keys four or two ways.
-  // At 64 workgroups of 256 queries, 4096 keys: d = 128 88 us whole, 54 two ways, 45 four ways;
-  // d = 64 66, 40 and 28.  Past one round splitting loses (128: 71 two ways, 85 four ways; 192:
-  // 105 whole, 120 two ways), because a tile then serves fewer queries.  Partials, which split over
-  // chunks already, take two ways at most.
-  if (n <= 64 && !partials) p.ks = 4;
-  else if (n <= 128) p.ks = 2;
-  while (p.ks > 1 && a.Nk / p.rg < 64 * p.ks) p.ks /= 2;
-  // A last round at most half full costs as much as a full one; workgroups of half the size end
-  // closer together (320: d = 64 140 -> 108 us at 4096 keys, d = 128 209 -> 188; 384: 139 -> 116,
-  // 205 -> 197), but read every tile for half the queries, which is 2-3% slower where the rounds
-  // are full and gains nothing past a few of them (640: 215 -> 187, 334 -> 326; 1024: even).
-  p.half = n > 256 && n < 1024 && (n - 1) % 256 < 128;
+  p.cut = query_cut(n * p.rg, a.Nk / p.rg);
+  // partials, which split over chunks already, take two streams at most (four 128-key chunks of 4
+  // heads x 512 queries: 8.9 us four ways, 10.2 two ways, 12.3 whole)
+  if (partials && p.cut.ks > 2) p.cut.ks = 2;
   return p;
 }
 
 template <int D, int MODE>
 hipError_t launch_plan(const FwdArgs& a) {
   const FwdPlan p = plan(a, MODE == (int)FwdMode::kPartials);
-  if (p.half) return launch<D, MODE, 1, 4>(a, p.rg);
+  if (p.cut.half) return launch<D, MODE, 1, 4>(a, p.rg);
   if constexpr (MODE != (int)FwdMode::kPartials)
-    if (p.ks == 4) return launch<D, MODE, 4, 8>(a, p.rg);
-  if (p.ks == 2) return launch<D, MODE, 2, 8>(a, p.rg);
+    if (p.cut.ks == 4) return launch<D, MODE, 4, 8>(a, p.rg);
+  if (p.cut.ks == 2) return launch<D, MODE, 2, 8>(a, p.rg);
   return launch<D, MODE, 1, 8>(a, p.rg);
 }
 

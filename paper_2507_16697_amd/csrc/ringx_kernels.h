@@ -14,6 +14,34 @@ enum class FwdMode {
   kStep = 2,      // R = 1: merge the one chunk into the running fp32 acc_out, acc_lse
 };
 
+// How the query-stationary bf16 kernels (forward, dQ) cut a launch.  Whole: workgroups of 256
+// queries, one per CU, so n of them take ceil(n / 256) rounds, and with few of them, or few in the
+// last round, most of the chip is idle.
+struct QueryCut {
+  int ks = 1;          // key streams: an 8-wave workgroup takes 256 / ks queries, its waves split the
+                       // keys ks ways
+  bool half = false;   // 4-wave workgroups of 128 queries, two or three per CU
+};
+// n = B H ceil(Nq / 256); `keys` that one workgroup visits.  Measured at 4096 keys (us):
+//   n =            64           128          192          320          384        640
+//   forward d=64   66 40 28     66 45 53     69 80 77     140 108*     139 116*   215 187*
+//   forward d=128  88 54 45     89 71 85     105 120 126  209 188*     205 197*   334 326*
+//   dQ d=64        81 46 34     81 55 61     86 94 90     174 148*     176 155*   272 247*
+//   dQ d=128       138 81 64    139 100 114  147 164 170  294 264*     299 285*   464 454*
+//   (one, two and four streams; one stream and *half).  So: four streams as long as one round
+// holds the quarter-size workgroups, two while it holds the half-size ones, whole ones above (a
+// split workgroup reads every tile for fewer queries), and half-size workgroups where the last
+// round is at most half full: they end closer together, but where the rounds are full they are up
+// to 4% slower (dQ d = 128 at n = 1024: 671 and 700), and past four rounds nothing is left to gain.
+inline QueryCut query_cut(int64_t n, int64_t keys) {
+  QueryCut c;
+  if (n <= 64) c.ks = 4;
+  else if (n <= 128) c.ks = 2;
+  while (c.ks > 1 && keys < 64 * c.ks) c.ks /= 2;
+  c.half = n > 256 && n < 1024 && (n - 1) % 256 < 128;
+  return c;
+}
+
 struct FwdArgs {
   const void* q = nullptr;
   const void* k = nullptr;
@@ -113,7 +141,8 @@ hipError_t launch_bwd_pre(const BwdArgs& a, bool bf16);
 hipError_t launch_bwd_dkdv_bf16(const BwdArgs& a);
 hipError_t launch_bwd_dkdv_bf16_d64(const BwdArgs& a);   // d = 64 (bwd_bf16_d64.hip)
 hipError_t launch_bwd_dq_bf16(const BwdArgs& a);
-hipError_t launch_bwd_dq_bf16_d64(const BwdArgs& a);   // d = 64 (bwd_dq_bf16_d64.hip)
+// d = 64, and d = 128 where the launch is cut (bwd_dq_bf16_d64.hip)
+hipError_t launch_bwd_dq_bf16_two_waves(const BwdArgs& a, const QueryCut& c);
 hipError_t launch_bwd_dkdv_f32(const BwdArgs& a);
 hipError_t launch_bwd_dq_f32(const BwdArgs& a);
 hipError_t launch_bwd_f32(const BwdArgs& a);      // both halves of the fp32 backward
