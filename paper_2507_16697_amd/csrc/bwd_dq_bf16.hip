@@ -1,5 +1,5 @@
 // Recompute backward of ring-chunked attention, dQ part at head size 128: bf16 MFMA with fp32
-// accumulation (gfx950).  Head size 64, and launches that have to be cut into smaller workgroups,
+// accumulation (gfx950).  Head size 64, and launches whose workgroups split the keys,
 // run the two-waves-per-SIMD kernel in bwd_dq_bf16_d64.hip.
 //
 // Query-stationary, like the forward: one workgroup = 4 waves (one per SIMD) = one (b, h) and 256
@@ -419,9 +419,9 @@ hipError_t launch(const BwdArgs& a) {
 }  // namespace
 
 hipError_t launch_bwd_dq_bf16(const BwdArgs& a) {
-  const QueryCut c = query_cut((a.Nq + 255) / 256 * a.BH, a.Nk);
-  if (a.d == 128 && c.ks == 1 && !c.half) return launch<128>(a);
-  return launch_bwd_dq_bf16_two_waves(a, c);
+  const QueryCut c = query_cut((a.Nq + 255) / 256 * a.BH, a.Nk, false);
+  if (a.d == 128 && c.ks == 1) return launch<128>(a);
+  return launch_bwd_dq_bf16_two_waves(a, c.ks);
 }
 
 }  // namespace ringx

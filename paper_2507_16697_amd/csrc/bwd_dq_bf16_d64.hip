@@ -26,12 +26,12 @@ namespace {
 
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-// KS key streams share a workgroup's NW waves (KS = 1: all of them take every tile).
-template <int D, int KS, int NW>
+// KS key streams share a workgroup's waves (KS = 1: all of them take every tile).
+template <int D, int KS>
 struct DqCfg {
   static constexpr int kD = D;
-  static constexpr int kThreads = 64 * NW;
-  static constexpr int kWaves = NW;
+  static constexpr int kThreads = 512;
+  static constexpr int kWaves = 8;
   static constexpr int kSW = kWaves / KS;          // waves per key stream
   static constexpr int kQW = 32;
   static constexpr int kBQ = kSW * kQW;
@@ -106,21 +106,21 @@ __device__ __forceinline__ void issue_tile(const char* __restrict__ kb,
 
 // With KS > 1 key streams, stream p of the workgroup takes every KS-th key tile, and the streams'
 // dQ^T meet in LDS at the end.
-template <int D, int KS, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dq_kernel(
+template <int D, int KS>
+__global__ __launch_bounds__(512, 1) void bwd_dq_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ lse,
     const float* __restrict__ delta, float* __restrict__ dq, int BH, int H, int grp, int64_t Nq,
     int64_t Nk, int R, float c2, float scale, int accumulate) {
-  using C = DqCfg<D, KS, NW>;
+  using C = DqCfg<D, KS>;
   // per stream two K buffers, then two V buffers
   __shared__ __attribute__((aligned(1024))) char lds[4 * KS * C::kTileBytes];
 
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int wave8 = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int ks = wave8 / C::kSW;      // key stream
-  const int wave = wave8 % C::kSW;    // wave of the stream
+  const int ks = KS == 1 ? 0 : wave8 / C::kSW;           // key stream
+  const int wave = KS == 1 ? wave8 : wave8 % C::kSW;     // wave of the stream
   const char* const lds_k = lds + 4 * ks * C::kTileBytes;
   const char* const lds_v = lds_k + 2 * C::kTileBytes;
   const int n = lane & 31;
@@ -359,12 +359,12 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dq_kernel(
   }
 }
 
-template <int D, int KS, int NW>
+template <int D, int KS>
 hipError_t launch(const BwdArgs& a) {
-  using C = DqCfg<D, KS, NW>;
+  using C = DqCfg<D, KS>;
   const int64_t nqt = (a.Nq + C::kBQ - 1) / C::kBQ;
   const int64_t nwg = nqt * a.BH;
-  hipLaunchKernelGGL((bwd_dq_kernel<D, KS, NW>), dim3((uint32_t)nwg), dim3(C::kThreads), 0,
+  hipLaunchKernelGGL((bwd_dq_kernel<D, KS>), dim3((uint32_t)nwg), dim3(C::kThreads), 0,
                      a.stream, (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v,
                      (const __bf16*)a.dout, a.lse, a.delta, a.dq, (int)a.BH, (int)a.H, (int)a.G,
                      a.Nq, a.Nk, (int)a.R, a.scale * kLog2e, a.scale, a.accumulate_dq ? 1 : 0);
@@ -373,15 +373,11 @@ hipError_t launch(const BwdArgs& a) {
 
 }  // namespace
 
-hipError_t launch_bwd_dq_bf16_two_waves(const BwdArgs& a, const QueryCut& c) {
-  if (a.d == 128) {
-    if (c.half) return launch<128, 1, 4>(a);
-    return c.ks == 4 ? launch<128, 4, 8>(a) : launch<128, 2, 8>(a);
-  }
-  if (c.half) return launch<64, 1, 4>(a);
-  if (c.ks == 4) return launch<64, 4, 8>(a);
-  if (c.ks == 2) return launch<64, 2, 8>(a);
-  return launch<64, 1, 8>(a);
+hipError_t launch_bwd_dq_bf16_two_waves(const BwdArgs& a, int ks) {
+  if (a.d == 128) return ks == 4 ? launch<128, 4>(a) : launch<128, 2>(a);
+  if (ks == 4) return launch<64, 4>(a);
+  if (ks == 2) return launch<64, 2>(a);
+  return launch<64, 1>(a);
 }
 
 }  // namespace ringx

@@ -137,7 +137,7 @@ __device__ __forceinline__ void issue_tile(const char* __restrict__ base, uint32
 // workgroup takes every KS-th key tile of the range (the whole range in fused and step mode, one
 // chunk after the other in partials mode) and the streams merge through LDS at its end.
 template <int D, int MODE, int KS, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : D == 64 ? 3 : 2) void fwd_bf16_kernel(
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void fwd_bf16_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     __bf16* __restrict__ out, float* __restrict__ lse, float* __restrict__ part_out,
     float* __restrict__ part_lse, float* __restrict__ acc_out, float* __restrict__ acc_lse,
@@ -154,8 +154,8 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : D == 64 ? 3 : 2) void fwd_bf
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int wave8 = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int ks = wave8 / C::kSW;      // key stream
-  const int wave = wave8 % C::kSW;    // wave of the stream
+  const int ks = KS == 1 ? 0 : wave8 / C::kSW;           // key stream
+  const int wave = KS == 1 ? wave8 : wave8 % C::kSW;     // wave of the stream
   const int n = lane & 31;
   const int g = lane >> 5;
 
@@ -473,28 +473,20 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : D == 64 ? 3 : 2) void fwd_bf
     }
     __builtin_amdgcn_sched_barrier(0);
 
-    if (KS == 1 && t0.start + C::kBK >= t0.hi) {
-      // end of chunk r0: loc_lse_r from the chunk's own row sum
-      const float lrow = sum_halves(lc);
-      const float lse2r = m2 + fast_log2(lrow);
-      if constexpr (kFused) {
-        // Eq. (5) on the log-sum-exps; the numerator terms already share the reference m2
-        const float M = fmaxf(lse2m, lse2r);
-        lse2m = M + fast_log2(fast_exp2(lse2m - M) + fast_exp2(lse2r - M));
-      } else {
-        if constexpr (kStep) put_step(lrow, lse2r);
-        else put_partial(r0, lrow, lse2r);
-#pragma unroll
-        for (int c = 0; c < C::kCT; ++c) oacc[c] = f32x16{};
-        m2 = -INFINITY;
-      }
+    // the last tile of its chunk?  (step mode has one chunk, whose end is the loop's)
+    const bool chunk_end = KS == 1 && !kStep && t0.start + C::kBK >= t0.hi;
+    if (kFused && chunk_end) {
+      // end of chunk r0: loc_lse_r from the chunk's own row sum, merged by Eq. (5) on the
+      // log-sum-exps; the numerator terms already share the reference m2
+      const float lse2r = m2 + fast_log2(sum_halves(lc));
+      const float M = fmaxf(lse2m, lse2r);
+      lse2m = M + fast_log2(fast_exp2(lse2m - M) + fast_exp2(lse2r - M));
       lc = 0.f;
-      ++r0;
     }
     t0 = t1;
     t1 = t2;
     t2 = next_tile(t2);
-    if constexpr (KS == 1) return t0.start >= key_end;
+    if constexpr (KS == 1) return kPartials ? chunk_end : t0.start >= key_end;
     else return ++it >= nit;
   };
   auto run_range = [&] {
@@ -505,8 +497,36 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : D == 64 ? 3 : 2) void fwd_bf
     }
   };
 
-  if constexpr (KS == 1) {
+  if constexpr (KS == 1 && kPartials) {
+    // Chunk ends leave the tile loop and come back to it where they left, pipeline intact: with
+    // the stores inside the loop the compiler orders the exponentials so that each waits for its
+    // own result (26 wait states per tile at d = 64).
+    first_scores();
+    bool odd = false;
+    while (true) {
+      while (true) {
+        if (!odd) {
+          odd = true;
+          if (step(sa, sb, std::integral_constant<int, 0>{})) break;
+        }
+        odd = false;
+        if (step(sb, sa, std::integral_constant<int, 1>{})) break;
+      }
+      const float lrow = sum_halves(lc);
+      put_partial(r0, lrow, m2 + fast_log2(lrow));
+      if (t0.start >= key_end) break;
+#pragma unroll
+      for (int c = 0; c < C::kCT; ++c) oacc[c] = f32x16{};
+      m2 = -INFINITY;
+      lc = 0.f;
+      ++r0;
+    }
+  } else if constexpr (KS == 1) {
     run_range();
+    if constexpr (kStep) {
+      const float lrow = sum_halves(lc);
+      put_step(lrow, m2 + fast_log2(lrow));
+    }
   } else {
     while (true) {
       const uint32_t hi = key_end;
@@ -616,14 +636,14 @@ struct FwdPlan {
   int64_t rg = 1;   // chunk groups (partials)
 };
 
-FwdPlan plan(const FwdArgs& a, bool partials) {
+FwdPlan plan(const FwdArgs& a, bool partials, bool can_half) {
   FwdPlan p;
   const int64_t n = (a.Nq + 255) / 256 * a.BH;
   // Partials: chunks are independent, so they are spread over workgroups until there are four
   // rounds (Nq = 2048, 8 chunks of 4096, 16 heads, d = 128: 664 -> 453 us).
   if (partials)
     while (p.rg < a.R && n * p.rg < 1024) p.rg = std::min<int64_t>(2 * p.rg, a.R);
-  p.cut = query_cut(n * p.rg, a.Nk / p.rg);
+  p.cut = query_cut(n * p.rg, a.Nk / p.rg, can_half);
   // partials, which split over chunks already, take two streams at most (four 128-key chunks of 4
   // heads x 512 queries: 8.9 us four ways, 10.2 two ways, 12.3 whole)
   if (partials && p.cut.ks > 2) p.cut.ks = 2;
@@ -632,8 +652,9 @@ FwdPlan plan(const FwdArgs& a, bool partials) {
 
 template <int D, int MODE>
 hipError_t launch_plan(const FwdArgs& a) {
-  const FwdPlan p = plan(a, MODE == (int)FwdMode::kPartials);
-  if (p.cut.half) return launch<D, MODE, 1, 4>(a, p.rg);
+  const FwdPlan p = plan(a, MODE == (int)FwdMode::kPartials, D == 64);
+  if constexpr (D == 64)
+    if (p.cut.half) return launch<D, MODE, 1, 4>(a, p.rg);
   if constexpr (MODE != (int)FwdMode::kPartials)
     if (p.cut.ks == 4) return launch<D, MODE, 4, 8>(a, p.rg);
   if (p.cut.ks == 2) return launch<D, MODE, 2, 8>(a, p.rg);
