@@ -4,13 +4,13 @@
 // kernel runs two waves per SIMD, each hiding its vector work behind the other's products (the
 // d = 128 kernel in bwd_bf16.hip runs one wave per SIMD on a fixed software-pipelined schedule).
 //
-// One workgroup = 8 waves = one K/V head and a tile of 128 keys inside one chunk (a key tile never
-// straddles a chunk boundary).  With the merged log-sum-exp saved by the forward, every chunk's
+// One workgroup = 8 (or 4) waves = one K/V head and a tile of 128 (64) keys inside one chunk (a key
+// tile never straddles a chunk boundary; the launch rule is at the end of the file).  With the merged log-sum-exp saved by the forward, every chunk's
 // gradients are independent (arXiv 2507.16697 Sec. III-A: K/V chunk gradients computed per
-// chunk), so the workgroup sweeps every query tile of 128 queries once -- of every query head that
-// shares the K/V head when G > 1 query heads share one (grouped-query attention).  Wave w owns keys
-// 32*(w%4) .. +31 of the tile and query half w/4 of every query tile, and keeps fp32 dK^T, dV^T
-// accumulators for its keys in registers.  Per query tile:
+// chunk), so the workgroup sweeps every query tile of 64 or 128 queries once -- of every query head
+// that shares the K/V head when G > 1 query heads share one (grouped-query attention).  Of 2 B waves,
+// wave w owns keys 32*(w%B) .. +31 of the tile and query half w/B of every query tile, and keeps
+// fp32 dK^T, dV^T accumulators for its keys in registers.  Per query tile:
 //   S    = Q K^T        A = Q rows (LDS),  B = K rows (LDS)             -> lane = key
 //   D-dP = D + dO (-V)^T A = dO rows (LDS), B = -V rows (LDS), accumulators start at D
 //   P    = exp2(S*scale*log2e + nl_i),  -dS = P (D - dP)                (fp32; nl_i = -lse_i*log2e
@@ -33,14 +33,16 @@ namespace {
 
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-template <int D>
+// NW waves = KB key blocks of 32 keys x two halves of the query tile; QB 32-query blocks per wave.
+template <int D, int NW, int QB>
 struct DkvCfg {
-  static constexpr int kThreads = 512;
-  static constexpr int kWaves = 8;
-  static constexpr int kBK = 128;                  // keys per workgroup (32 per key block)
-  static constexpr int kBQ = 8192 / D;             // queries per tile: 64 (d=128), 128 (d=64)
-  static constexpr int kQW = kBQ / 2;              // queries per wave
-  static constexpr int kQB = kQW / 32;             // 32-query blocks per wave
+  static constexpr int kThreads = 64 * NW;
+  static constexpr int kWaves = NW;
+  static constexpr int kKB = NW / 2;               // key blocks
+  static constexpr int kBK = 32 * kKB;             // keys per workgroup
+  static constexpr int kQB = QB;                   // 32-query blocks per wave
+  static constexpr int kQW = 32 * kQB;             // queries per wave
+  static constexpr int kBQ = 2 * kQW;              // queries per tile
   static constexpr int kRowBytes = 2 * D;          // Q, dO, K, V rows
   static constexpr int kDSteps = D / 16;
   static constexpr int kCT = D / 32;
@@ -57,8 +59,8 @@ struct DkvCfg {
   static constexpr int kOffD = kOffL + 2 * kBQ * 4;     // 2 x kBQ floats: D
   static constexpr int kLds = kOffD + 2 * kBQ * 4;
   static_assert(kOffK <= 65536, "Q / dO buffers within the LDS immediate offset");
-  static_assert(kQB * 32 * 2 == kBQ, "two query halves");
-  static_assert(4 * kQTile >= kWaves / 2 * kCT * 16 * 64 * 4, "dK/dV exchange fits");
+  static_assert(kBQ <= 128, "nl and D of a tile by two waves each");
+  static_assert(4 * kQTile >= kKB * kCT * 16 * 64 * 4, "dK/dV exchange fits");
 };
 
 // XOR swizzle of the 16-byte chunks of a row of `RB` bytes (as in the forward kernel): 16
@@ -114,14 +116,14 @@ __device__ __forceinline__ void issue_rowvals(const float* __restrict__ nlb,
   }
 }
 
-template <int D>
-__global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(
+template <int D, int NW, int QB>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ nl,
     const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv, int BHkv,
     int H, int grp,
     int64_t Nq, int64_t Nk, int R, int tiles_per_chunk, float c2, float scale, int accumulate) {
-  using C = DkvCfg<D>;
+  using C = DkvCfg<D, NW, QB>;
   __shared__ __attribute__((aligned(1024))) char lds[C::kLds];
   const uint32_t lbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
@@ -130,8 +132,8 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int n = lane & 31;
   const int g = lane >> 5;
-  const int kb = wave & 3;          // key block of this wave
-  const int qh = wave >> 2;         // query half of this wave
+  const int kb = wave % C::kKB;     // key block of this wave
+  const int qh = wave / C::kKB;     // query half of this wave
 
   const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t per_bh = (int64_t)R * tiles_per_chunk;
@@ -170,8 +172,6 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(
   issue_rows<D>(ob, lbase + C::kOffO, nq - 1, C::kQTile / 1024 / C::kWaves, wave, lane,
                 C::kWaves);
   issue_rowvals<C::kBQ>(nlb, deltab, lbase + C::kOffL, lbase + C::kOffD, nq - 1, wave, lane);
-  const float* lds_l = reinterpret_cast<const float*>(lds + C::kOffL);
-  const float* lds_d = reinterpret_cast<const float*>(lds + C::kOffD);
 
   // per-lane LDS byte offsets (tile-relative)
   // S / dP: A = Q/dO rows (query qh*kQW + 32*b + n), B = K/V rows (key 32*kb + n); chunk 2s+g
@@ -410,14 +410,14 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(
   }
 }
 
-template <int D>
+template <int D, int NW, int QB>
 hipError_t launch(const BwdArgs& a) {
-  using C = DkvCfg<D>;
+  using C = DkvCfg<D, NW, QB>;
   const int64_t max_chunk = (a.Nk + a.R - 1) / a.R;
   const int64_t tpc = (max_chunk + C::kBK - 1) / C::kBK;
   const int64_t nwg = a.BH / a.G * a.R * tpc;
-  hipLaunchKernelGGL((bwd_dkdv_kernel<D>), dim3((uint32_t)nwg), dim3(C::kThreads), 0, a.stream,
-                     (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v,
+  hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, QB>), dim3((uint32_t)nwg), dim3(C::kThreads), 0,
+                     a.stream, (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v,
                      (const __bf16*)a.dout, a.nl, a.delta, a.dk, a.dv, (int)(a.BH / a.G),
                      (int)a.H, (int)a.G, a.Nq, a.Nk,
                      (int)a.R, (int)tpc, a.scale * kLog2e, a.scale, a.accumulate_dkv ? 1 : 0);
@@ -426,6 +426,23 @@ hipError_t launch(const BwdArgs& a) {
 
 }  // namespace
 
-hipError_t launch_bwd_dkdv_bf16_d64(const BwdArgs& a) { return launch<64>(a); }
+// n = 128-key tiles of the launch.  Three shapes of the workgroup (us at 8192 queries; 8 waves x 64
+// queries of a tile each / 8 waves x 32 / 4 waves x 32):
+//   n =     96    128   192   256   266   384   390   474   512   626   1024  2048
+//           110   119   123   133   258   236   267   276   260   377   515   1033
+//           128   136   138   144   219   221   242   263   254   371   500   1009
+//           96    110   126   141   190   205   290   296   282   326   526   1058
+// With 32 queries per wave the kernel needs 127 registers and 65 KiB of LDS, so two workgroups share
+// a CU and cover each other's barriers and loads: 2-3% faster where the chip is full (16384 queries
+// and keys, 16 heads: at 1000 queries 187 -> 162).  64-key workgroups of 4 waves (138 registers, 49
+// KiB, three per CU) end closer together where few tiles are left for the last round, and fill the
+// chip earlier.  Between half a round and one round a CU has one workgroup anyway, and 64 queries
+// per wave make fewer barriers.
+hipError_t launch_bwd_dkdv_bf16_d64(const BwdArgs& a) {
+  const int64_t n = a.BH / a.G * a.R * ds_tiles_per_chunk(a.Nk, a.R);
+  const bool ragged = n > 256 && n < 1024 && (n - 1) % 256 < 128;
+  if (n <= 128 || ragged) return launch<64, 4, 1>(a);
+  return n <= 256 ? launch<64, 8, 2>(a) : launch<64, 8, 1>(a);
+}
 
 }  // namespace ringx
