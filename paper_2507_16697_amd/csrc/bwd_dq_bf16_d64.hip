@@ -26,16 +26,17 @@ namespace {
 
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-// KS key streams share a workgroup's waves (KS = 1: all of them take every tile).
-template <int D, int KS>
+// KS key streams share a workgroup's NW waves (KS = 1: all of them take every tile).  4-wave
+// workgroups take 32-key tiles: 152 registers, so that three of them share a CU.
+template <int D, int KS, int NW, int BK>
 struct DqCfg {
   static constexpr int kD = D;
-  static constexpr int kThreads = 512;
-  static constexpr int kWaves = 8;
+  static constexpr int kThreads = 64 * NW;
+  static constexpr int kWaves = NW;
   static constexpr int kSW = kWaves / KS;          // waves per key stream
   static constexpr int kQW = 32;
   static constexpr int kBQ = kSW * kQW;
-  static constexpr int kBK = KS * D > 256 ? 32 : 64;   // keys per tile (LDS holds 4 KS tiles)
+  static constexpr int kBK = BK;                   // keys per tile (LDS holds 4 KS tiles)
   static constexpr int kRowBytes = D * 2;
   static constexpr int kChunks = D / 8;
   static constexpr int kTileBytes = kBK * kRowBytes;
@@ -106,13 +107,13 @@ __device__ __forceinline__ void issue_tile(const char* __restrict__ kb,
 
 // With KS > 1 key streams, stream p of the workgroup takes every KS-th key tile, and the streams'
 // dQ^T meet in LDS at the end.
-template <int D, int KS>
-__global__ __launch_bounds__(512, 1) void bwd_dq_kernel(
+template <int D, int KS, int NW, int BK>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void bwd_dq_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ lse,
     const float* __restrict__ delta, float* __restrict__ dq, int BH, int H, int grp, int64_t Nq,
     int64_t Nk, int R, float c2, float scale, int accumulate) {
-  using C = DqCfg<D, KS>;
+  using C = DqCfg<D, KS, NW, BK>;
   // per stream two K buffers, then two V buffers
   __shared__ __attribute__((aligned(1024))) char lds[4 * KS * C::kTileBytes];
 
@@ -359,12 +360,12 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_kernel(
   }
 }
 
-template <int D, int KS>
+template <int D, int KS, int NW, int BK>
 hipError_t launch(const BwdArgs& a) {
-  using C = DqCfg<D, KS>;
+  using C = DqCfg<D, KS, NW, BK>;
   const int64_t nqt = (a.Nq + C::kBQ - 1) / C::kBQ;
   const int64_t nwg = nqt * a.BH;
-  hipLaunchKernelGGL((bwd_dq_kernel<D, KS>), dim3((uint32_t)nwg), dim3(C::kThreads), 0,
+  hipLaunchKernelGGL((bwd_dq_kernel<D, KS, NW, BK>), dim3((uint32_t)nwg), dim3(C::kThreads), 0,
                      a.stream, (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v,
                      (const __bf16*)a.dout, a.lse, a.delta, a.dq, (int)a.BH, (int)a.H, (int)a.G,
                      a.Nq, a.Nk, (int)a.R, a.scale * kLog2e, a.scale, a.accumulate_dq ? 1 : 0);
@@ -373,11 +374,12 @@ hipError_t launch(const BwdArgs& a) {
 
 }  // namespace
 
-hipError_t launch_bwd_dq_bf16_two_waves(const BwdArgs& a, int ks) {
-  if (a.d == 128) return ks == 4 ? launch<128, 4>(a) : launch<128, 2>(a);
-  if (ks == 4) return launch<64, 4>(a);
-  if (ks == 2) return launch<64, 2>(a);
-  return launch<64, 1>(a);
+hipError_t launch_bwd_dq_bf16_two_waves(const BwdArgs& a, const QueryCut& c) {
+  if (a.d == 128) return c.ks == 4 ? launch<128, 4, 8, 32>(a) : launch<128, 2, 8, 64>(a);
+  if (c.half) return launch<64, 1, 4, 32>(a);
+  if (c.ks == 4) return launch<64, 4, 8, 64>(a);
+  if (c.ks == 2) return launch<64, 2, 8, 64>(a);
+  return launch<64, 1, 8, 64>(a);
 }
 
 }  // namespace ringx

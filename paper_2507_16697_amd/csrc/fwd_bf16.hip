@@ -636,14 +636,14 @@ struct FwdPlan {
   int64_t rg = 1;   // chunk groups (partials)
 };
 
-FwdPlan plan(const FwdArgs& a, bool partials, bool can_half) {
+FwdPlan plan(const FwdArgs& a, bool partials) {
   FwdPlan p;
   const int64_t n = (a.Nq + 255) / 256 * a.BH;
   // Partials: chunks are independent, so they are spread over workgroups until there are four
   // rounds (Nq = 2048, 8 chunks of 4096, 16 heads, d = 128: 664 -> 453 us).
   if (partials)
     while (p.rg < a.R && n * p.rg < 1024) p.rg = std::min<int64_t>(2 * p.rg, a.R);
-  p.cut = query_cut(n * p.rg, a.Nk / p.rg, can_half);
+  p.cut = query_cut(n * p.rg, a.Nk / p.rg, a.d == 64 ? HalfRule{512, 16384} : HalfRule{0, 0});
   // partials, which split over chunks already, take two streams at most (four 128-key chunks of 4
   // heads x 512 queries: 8.9 us four ways, 10.2 two ways, 12.3 whole)
   if (partials && p.cut.ks > 2) p.cut.ks = 2;
@@ -652,7 +652,7 @@ FwdPlan plan(const FwdArgs& a, bool partials, bool can_half) {
 
 template <int D, int MODE>
 hipError_t launch_plan(const FwdArgs& a) {
-  const FwdPlan p = plan(a, MODE == (int)FwdMode::kPartials, D == 64);
+  const FwdPlan p = plan(a, MODE == (int)FwdMode::kPartials);
   if constexpr (D == 64)
     if (p.cut.half) return launch<D, MODE, 1, 4>(a, p.rg);
   if constexpr (MODE != (int)FwdMode::kPartials)

@@ -20,26 +20,33 @@ enum class FwdMode {
 struct QueryCut {
   int ks = 1;          // key streams: an 8-wave workgroup takes 256 / ks queries, its waves split the
                        // keys ks ways
-  bool half = false;   // 4-wave workgroups of 128 queries, three per CU (forward, d = 64)
+  bool half = false;   // 4-wave workgroups of 128 queries, three per CU (d = 64)
 };
-// n = B H ceil(Nq / 256); `keys` that one workgroup visits; `can_half`: the kernel has half-size
-// workgroups.  Measured at 8192 keys, two heads (us; one, two and four streams, *half-size):
+// Where a kernel's half-size workgroups win although the rounds are full: n >= from, up to `keys`
+// keys.  from = 0: the kernel has none.
+struct HalfRule {
+  int64_t from, keys;
+};
+// n = B H ceil(Nq / 256); `keys` that one workgroup visits.  Measured at 8192 keys, two heads (us; one,
+// two and four streams, *half-size):
 //   n =            96           128          192          288              384              768
 //   forward d=64   130 84 96    123 82 92    127 148 136  260 222 195*     259 240 217*     422 458 419*
-//   forward d=128  178 127 152  168 130 152  200 222 230  388 338 354*     387 370 370*     679 731 694*
-//   dQ d=64        156 94 106   157 103 112  162 180 165  339 278 286*     339 298 299*     566 586 577*
-//   dQ d=128       263 157 199  263 181 212  270 311 316  575 485 527*     576 528 543*     963 1043 1029*
+//   forward d=128  178 127 152  168 130 152  200 222 230  388 338          387 370          679 731
+//   dQ d=64        156 94 106   157 103 112  162 180 165  327 275 249*     329 299 282*     566 586
+//   dQ d=128       263 157 199  263 181 212  270 311 316  575 485          576 528          963 1043
 // and at n = 64, 4096 keys: 66 40 28, 88 54 45, 81 46 34 and 138 81 64.  So: four streams as long
-// as one round holds the quarter-size workgroups, two while it holds the half-size ones, and where
-// the last round is at most half full, whose workgroups then end closer together (at 65536 keys,
-// six heads, n = 288: 3109 -> 2635, 2662 -> 2136 and 4767 -> 3945; n = 576: 4995 -> 4477); the
-// forward at d = 64, which fits three 4-wave workgroups on a CU, takes those there (2003 ->
-// 1498, two streams 1671).  Where the rounds are full splitting loses, because a tile serves fewer
-// queries, and past four of them nothing is left to gain.
-inline QueryCut query_cut(int64_t n, int64_t keys, bool can_half) {
+// as one round holds the quarter-size workgroups, two while it holds the half-size ones; where the
+// last round is at most half full, half-size workgroups, which end closer together, or two streams
+// for want of them (at 65536 keys, six heads, n = 288: 2003 -> 1498, 3109 -> 2635, 2598 -> 1927 and
+// 4767 -> 3945).  In full rounds splitting loses, because a tile serves fewer queries, unless three
+// half-size workgroups on a CU gain more by covering each other's barriers, first and last tiles:
+// the d = 64 forward does up to 16384 keys (n = 1024: 1024 keys 97 -> 85, 4096 301 -> 284, 16384
+// 1130 -> 1072; 2% slower at 262144), dQ up to 4096 keys and from three rounds on (1024 keys 118 ->
+// 110, n = 768 at 2048 keys 160 -> 153, n = 3072 at 4096 1138 -> 1108; n = 512 197 against 204).
+inline QueryCut query_cut(int64_t n, int64_t keys, HalfRule h) {
   QueryCut c;
   const bool ragged = n > 256 && n < 1024 && (n - 1) % 256 < 128;
-  if (ragged && can_half) c.half = true;
+  if (h.from > 0 && (ragged || (n >= h.from && keys <= h.keys))) c.half = true;
   else if (n <= 64) c.ks = 4;
   else if (n <= 128 || ragged) c.ks = 2;
   while (c.ks > 1 && keys < 64 * c.ks) c.ks /= 2;
@@ -146,7 +153,7 @@ hipError_t launch_bwd_dkdv_bf16(const BwdArgs& a);
 hipError_t launch_bwd_dkdv_bf16_d64(const BwdArgs& a);   // d = 64 (bwd_bf16_d64.hip)
 hipError_t launch_bwd_dq_bf16(const BwdArgs& a);
 // d = 64, and d = 128 where the launch is split into key streams (bwd_dq_bf16_d64.hip)
-hipError_t launch_bwd_dq_bf16_two_waves(const BwdArgs& a, int ks);
+hipError_t launch_bwd_dq_bf16_two_waves(const BwdArgs& a, const QueryCut& c);
 hipError_t launch_bwd_dkdv_f32(const BwdArgs& a);
 hipError_t launch_bwd_dq_f32(const BwdArgs& a);
 hipError_t launch_bwd_f32(const BwdArgs& a);      // both halves of the fp32 backward

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 # (H, Nq, Nk, R): dQ is cut by n = H ceil(Nq / 256)
 DQ = [(1, 1, 1, 1), (1, 65, 255, 2), (3, 64, 256, 5), (2, 300, 257, 1), (1, 257, 700, 700),
       (64, 40, 300, 3), (65, 70, 127, 1), (65, 70, 128, 4), (128, 129, 200, 3), (129, 40, 100, 2),
-      (257, 70, 130, 3), (192, 300, 66, 1)]
+      (257, 70, 130, 3), (192, 300, 66, 1), (768, 5, 40, 2)]
 # dK/dV at d = 64 is cut by n = H R ceil(ceil(Nk / R) / 128) 128-key tiles
 DKDV = [(1, 63, 63, 1), (2, 64, 65, 1), (4, 129, 1000, 8), (65, 40, 200, 2), (128, 33, 129, 1),
         (130, 31, 260, 1), (129, 65, 128, 4), (300, 20, 300, 1)]

@@ -24,7 +24,7 @@ FOUR = [(1, 1, 1, 1), (2, 33, 64, 1), (1, 65, 255, 2), (3, 64, 256, 5), (2, 300,
         (1, 257, 700, 700), (64, 40, 300, 3)]
 TWO = [(65, 70, 127, 1), (65, 70, 128, 4), (128, 129, 200, 3)]
 WHOLE = [(129, 40, 100, 2), (256, 33, 65, 1)]
-HALF = [(257, 70, 130, 3), (192, 300, 66, 1), (700, 20, 33, 2)]
+HALF = [(257, 70, 130, 3), (192, 300, 66, 1), (512, 20, 33, 2), (1025, 3, 65, 1)]
 GROUPS = [(40, 300, 150, 20), (3, 90, 150, 150), (130, 20, 300, 9), (300, 20, 70, 3)]
 
 
