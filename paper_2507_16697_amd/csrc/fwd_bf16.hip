@@ -639,10 +639,17 @@ struct FwdPlan {
 FwdPlan plan(const FwdArgs& a, bool partials) {
   FwdPlan p;
   const int64_t n = (a.Nq + 255) / 256 * a.BH;
-  // Partials: chunks are independent, so they are spread over workgroups until there are four
-  // rounds (Nq = 2048, 8 chunks of 4096, 16 heads, d = 128: 664 -> 453 us).
-  if (partials)
-    while (p.rg < a.R && n * p.rg < 1024) p.rg = std::min<int64_t>(2 * p.rg, a.R);
+  // Partials: chunks are independent, so they are spread over workgroups, over as few groups as give
+  // the fewest rounds for their length (480 workgroups, whose two rounds are nearly full, lose 2% to
+  // four groups), and up to four rounds where one is at most half full (Nq = 2048, 8 chunks of 4096,
+  // 16 heads, d = 128: 664 us whole, 479 in one round, 453 in four).
+  if (partials) {
+    auto rounds = [n](int64_t rg) { return (double)((n * rg + 255) / 256) / (double)rg; };
+    for (int64_t rg = 1; rg < a.R && n * rg < 2048;) {
+      rg = std::min<int64_t>(2 * rg, a.R);
+      if (rounds(rg) < 0.98 * rounds(p.rg) || (n <= 128 && n * rg <= 1024)) p.rg = rg;
+    }
+  }
   p.cut = query_cut(n * p.rg, a.Nk / p.rg, a.d == 64 ? HalfRule{512, 16384} : HalfRule{0, 0});
   // partials, which split over chunks already, take two streams at most (four 128-key chunks of 4
   // heads x 512 queries: 8.9 us four ways, 10.2 two ways, 12.3 whole)
