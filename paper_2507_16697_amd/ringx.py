@@ -149,18 +149,27 @@ def ringx_bwd_ds_workspace_bytes(B, H, Hkv, Nq, Nk, d, R, kv_per_slab) -> int:
 # torch tensor helpers
 
 
+_T = None          # torch, imported on first use
+_raw_stream = None  # device index -> handle of its current stream, where torch offers it
+
+
 def _torch():
-    import torch
-    return torch
+    global _T, _raw_stream
+    if _T is None:
+        import torch
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _T = torch
+    return _T
 
 
 def _dtype_code(t) -> int:
-    torch = _torch()
-    if t.dtype == torch.bfloat16:
+    torch = _T or _torch()
+    dtype = t.dtype
+    if dtype is torch.bfloat16:
         return RINGX_BF16
-    if t.dtype == torch.float32:
+    if dtype is torch.float32:
         return RINGX_FP32
-    raise TypeError(f"unsupported dtype {t.dtype}; expected bfloat16 or float32")
+    raise TypeError(f"unsupported dtype {dtype}; expected bfloat16 or float32")
 
 
 def _dev(*ts):
@@ -174,12 +183,28 @@ def _dev(*ts):
 def _expect(name, t, shape, dtype, device):
     """The kernels size every buffer from q and k: a tensor of another shape, dtype or device
     would be read or written out of bounds, so it is refused here."""
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:   # a torch.Size compares as a tuple
         raise ValueError(f"{name}: shape {tuple(t.shape)}, expected {tuple(shape)}")
-    if t.dtype != dtype:
+    if t.dtype is not dtype:
         raise TypeError(f"{name}: dtype {t.dtype}, expected {dtype}")
     if t.device != device:
         raise ValueError(f"{name}: on {t.device}, expected {device}")
+
+
+def _out(name, t, shape, dtype, like):
+    """The caller's output buffer, checked, or a new one on `like`'s device."""
+    if t is None:
+        return like.new_empty(shape, dtype=dtype)
+    _dev(t)
+    _expect(name, t, shape, dtype, like.device)
+    return t
+
+
+def _grad_out(name, t, shape, like, accumulate):
+    """An fp32 gradient buffer that the call overwrites, or adds to (then a new one starts at 0)."""
+    if t is None and accumulate:
+        return like.new_zeros(shape, dtype=_T.float32)
+    return _out(name, t, shape, _T.float32, like)
 
 
 def _qkv(q, k, v, heads_kv=None):
@@ -189,29 +214,35 @@ def _qkv(q, k, v, heads_kv=None):
         raise ValueError("q, k and v must be 4-D [B, H, N, d]")
     _dtype_code(q)
     B, H, Nq, d = q.shape
-    Hkv, Nk = k.shape[1], k.shape[2]
+    _, Hkv, Nk, _ = k.shape
     if heads_kv is None and Hkv != H:
         raise ValueError(f"k has {Hkv} heads, q has {H}")
-    _expect("k", k, (B, Hkv, Nk, d), q.dtype, q.device)
-    _expect("v", v, (B, Hkv, Nk, d), q.dtype, q.device)
+    kv, dtype, device = (B, Hkv, Nk, d), q.dtype, q.device
+    _expect("k", k, kv, dtype, device)
+    _expect("v", v, kv, dtype, device)
     return B, H, Hkv, Nq, Nk, d
 
 
 def _check_grad_inputs(q, dout, lse, delta):
-    torch = _torch()
+    torch = _T or _torch()
     B, H, Nq, _ = q.shape
-    _expect("dout", dout, q.shape, q.dtype, q.device)
-    _expect("lse", lse, (B, H, Nq), torch.float32, q.device)
-    _expect("delta", delta, (2, B, H, Nq), torch.float32, q.device)
+    device = q.device
+    _expect("dout", dout, q.shape, q.dtype, device)
+    _expect("lse", lse, (B, H, Nq), torch.float32, device)
+    _expect("delta", delta, (2, B, H, Nq), torch.float32, device)
 
 
 def _stream(stream):
-    torch = _torch()
+    torch = _T or _torch()
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # the current stream of the current device (asking torch for the handle alone takes a tenth
+        # of the time of building a Stream object)
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
+        return torch.cuda.current_stream().cuda_stream
     if hasattr(stream, "cuda_stream"):
-        return ctypes.c_void_p(stream.cuda_stream)
-    return ctypes.c_void_p(int(stream))
+        return stream.cuda_stream
+    return int(stream)
 
 
 def _scale(scale, d):
@@ -220,16 +251,11 @@ def _scale(scale, d):
 
 def ringx_attn_fwd(q, k, v, R: int, scale=None, out=None, lse=None, stream=None):
     """Merged ring-chunked forward.  Returns (out [B,H,Nq,d] in q's dtype, lse [B,H,Nq] fp32)."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v)
     B, H, _, Nq, Nk, d = _qkv(q, k, v)
-    if out is None:
-        out = torch.empty_like(q)
-    if lse is None:
-        lse = torch.empty((B, H, Nq), dtype=torch.float32, device=q.device)
-    _dev(out, lse)
-    _expect("out", out, q.shape, q.dtype, q.device)
-    _expect("lse", lse, (B, H, Nq), torch.float32, q.device)
+    out = _out("out", out, q.shape, q.dtype, q)
+    lse = _out("lse", lse, (B, H, Nq), torch.float32, q)
     st = lib().ringx_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                               lse.data_ptr(), B, H, Nq, Nk, d, R, _scale(scale, d),
                               _dtype_code(q), _stream(stream))
@@ -240,16 +266,11 @@ def ringx_attn_fwd(q, k, v, R: int, scale=None, out=None, lse=None, stream=None)
 def ringx_attn_fwd_partials(q, k, v, R: int, scale=None, part_out=None, part_lse=None,
                             stream=None):
     """Per-chunk local results: (part_out [R,B,H,Nq,d] fp32, part_lse [R,B,H,Nq] fp32)."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v)
     B, H, _, Nq, Nk, d = _qkv(q, k, v)
-    if part_out is None:
-        part_out = torch.empty((R, B, H, Nq, d), dtype=torch.float32, device=q.device)
-    if part_lse is None:
-        part_lse = torch.empty((R, B, H, Nq), dtype=torch.float32, device=q.device)
-    _dev(part_out, part_lse)
-    _expect("part_out", part_out, (R, B, H, Nq, d), torch.float32, q.device)
-    _expect("part_lse", part_lse, (R, B, H, Nq), torch.float32, q.device)
+    part_out = _out("part_out", part_out, (R, B, H, Nq, d), torch.float32, q)
+    part_lse = _out("part_lse", part_lse, (R, B, H, Nq), torch.float32, q)
     st = lib().ringx_attn_fwd_partials(q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                        part_out.data_ptr(), part_lse.data_ptr(), B, H, Nq, Nk, d,
                                        R, _scale(scale, d), _dtype_code(q), _stream(stream))
@@ -259,7 +280,7 @@ def ringx_attn_fwd_partials(q, k, v, R: int, scale=None, part_out=None, part_lse
 
 def ringx_lse_merge(part_out, part_lse, out_dtype=None, out=None, lse=None, stream=None):
     """Eq. (5) merge of R partials.  Returns (out [B,H,Nq,d] in out_dtype, lse [B,H,Nq] fp32)."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(part_out, part_lse)
     if part_out.dim() != 5:
         raise ValueError("part_out must be 5-D [R, B, H, Nq, d]")
@@ -267,14 +288,9 @@ def ringx_lse_merge(part_out, part_lse, out_dtype=None, out=None, lse=None, stre
     dev = part_out.device
     _expect("part_out", part_out, (R, B, H, Nq, d), torch.float32, dev)
     _expect("part_lse", part_lse, (R, B, H, Nq), torch.float32, dev)
-    if out is None:
-        out = torch.empty((B, H, Nq, d), dtype=out_dtype or torch.float32, device=dev)
-    if lse is None:
-        lse = torch.empty((B, H, Nq), dtype=torch.float32, device=dev)
-    _dev(out, lse)
-    _dtype_code(out)
-    _expect("out", out, (B, H, Nq, d), out.dtype, dev)
-    _expect("lse", lse, (B, H, Nq), torch.float32, dev)
+    out = _out("out", out, (B, H, Nq, d),
+               (out_dtype or torch.float32) if out is None else out.dtype, part_out)
+    lse = _out("lse", lse, (B, H, Nq), torch.float32, part_out)
     st = lib().ringx_lse_merge(part_out.data_ptr(), part_lse.data_ptr(), out.data_ptr(),
                                lse.data_ptr(), R, B, H, Nq, d, _dtype_code(out), _stream(stream))
     _check("ringx_lse_merge", st)
@@ -284,34 +300,28 @@ def ringx_lse_merge(part_out, part_lse, out_dtype=None, out=None, lse=None, stre
 def ringx_attn_bwd(q, k, v, out, dout, lse, R: int, scale=None, dq=None, dk=None, dv=None,
                    accumulate_dkv=False, workspace=None, stream=None):
     """Recompute backward.  Returns fp32 (dq, dk, dv); dk/dv are added to when accumulate_dkv."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v, out, dout, lse)
     B, H, _, Nq, Nk, d = _qkv(q, k, v)
     _expect("out", out, q.shape, q.dtype, q.device)
     _expect("dout", dout, q.shape, q.dtype, q.device)
     _expect("lse", lse, (B, H, Nq), torch.float32, q.device)
-    f32 = dict(dtype=torch.float32, device=q.device)
-    if dq is None:
-        dq = torch.empty((B, H, Nq, d), **f32)
-    if dk is None:
-        dk = torch.zeros((B, H, Nk, d), **f32) if accumulate_dkv else torch.empty((B, H, Nk, d), **f32)
-    if dv is None:
-        dv = torch.zeros((B, H, Nk, d), **f32) if accumulate_dkv else torch.empty((B, H, Nk, d), **f32)
+    dq = _out("dq", dq, (B, H, Nq, d), torch.float32, q)
+    dk = _grad_out("dk", dk, (B, H, Nk, d), q, accumulate_dkv)
+    dv = _grad_out("dv", dv, (B, H, Nk, d), q, accumulate_dkv)
     code = _dtype_code(q)
-    need = ringx_bwd_workspace_bytes(B, H, Nq, Nk, d, R, code)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
-    _dev(dq, dk, dv, workspace)
-    _expect("dq", dq, (B, H, Nq, d), torch.float32, q.device)
-    _expect("dk", dk, (B, H, Nk, d), torch.float32, q.device)
-    _expect("dv", dv, (B, H, Nk, d), torch.float32, q.device)
-    if workspace.device != q.device:
-        raise ValueError(f"workspace: on {workspace.device}, expected {q.device}")
+        need = ringx_bwd_workspace_bytes(B, H, Nq, Nk, d, R, code)
+        workspace = q.new_empty(max(need, 16), dtype=torch.uint8)
+    else:
+        _dev(workspace)
+        if workspace.device != q.device:
+            raise ValueError(f"workspace: on {workspace.device}, expected {q.device}")
     st = lib().ringx_attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                               dout.data_ptr(), lse.data_ptr(), dq.data_ptr(), dk.data_ptr(),
                               dv.data_ptr(), B, H, Nq, Nk, d, R, _scale(scale, d), code,
                               1 if accumulate_dkv else 0, workspace.data_ptr(),
-                              workspace.numel() * workspace.element_size(), _stream(stream))
+                              _nbytes(workspace), _stream(stream))
     _check("ringx_attn_bwd", st)
     return dq, dk, dv
 
@@ -321,7 +331,7 @@ def ringx_attn_bwd_noalloc(q, k, v, out, dout, lse, R: int, dq, dk, dv, scale=No
     """ringx_attn_bwd for callers that cannot allocate: the caller passes the fp32 outputs dq, dk,
     dv, and D lives in the library's fixed device array (B * H * Nq <= NOALLOC_MAX_ROWS).  Calls
     that overlap in time on one GPU race on that array.  Returns (dq, dk, dv)."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v, out, dout, lse, dq, dk, dv)
     B, H, _, Nq, Nk, d = _qkv(q, k, v)
     _expect("out", out, q.shape, q.dtype, q.device)
@@ -342,7 +352,7 @@ def ringx_attn_bwd_noalloc(q, k, v, out, dout, lse, R: int, dq, dk, dv, scale=No
 def ringx_bwd_preprocess(out, dout, lse, delta=None, stream=None):
     """Per-row statistics delta [2,B,H,Nq] fp32: delta[0] = rowsum(dout * out),
     delta[1] = -lse * log2(e)."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(out, dout, lse)
     if out.dim() != 4:
         raise ValueError("out must be 4-D [B, H, Nq, d]")
@@ -350,10 +360,7 @@ def ringx_bwd_preprocess(out, dout, lse, delta=None, stream=None):
     B, H, Nq, d = out.shape
     _expect("dout", dout, out.shape, out.dtype, out.device)
     _expect("lse", lse, (B, H, Nq), torch.float32, out.device)
-    if delta is None:
-        delta = torch.empty((2, B, H, Nq), dtype=torch.float32, device=out.device)
-    _dev(delta)
-    _expect("delta", delta, (2, B, H, Nq), torch.float32, out.device)
+    delta = _out("delta", delta, (2, B, H, Nq), torch.float32, out)
     st = lib().ringx_bwd_preprocess(out.data_ptr(), dout.data_ptr(), lse.data_ptr(),
                                     delta.data_ptr(), B, H, Nq, d, _dtype_code(out),
                                     _stream(stream))
@@ -364,18 +371,12 @@ def ringx_bwd_preprocess(out, dout, lse, delta=None, stream=None):
 def ringx_attn_bwd_dkdv(q, k, v, dout, lse, delta, R: int, scale=None, dk=None, dv=None,
                         accumulate_dkv=False, stream=None):
     """Key/value gradients of every chunk.  Returns fp32 (dk, dv)."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v, dout, lse, delta)
     B, H, _, Nq, Nk, d = _qkv(q, k, v)
     _check_grad_inputs(q, dout, lse, delta)
-    f32 = dict(dtype=torch.float32, device=q.device)
-    if dk is None:
-        dk = torch.zeros((B, H, Nk, d), **f32)
-    if dv is None:
-        dv = torch.zeros((B, H, Nk, d), **f32)
-    _dev(dk, dv)
-    _expect("dk", dk, (B, H, Nk, d), torch.float32, q.device)
-    _expect("dv", dv, (B, H, Nk, d), torch.float32, q.device)
+    dk = _grad_out("dk", dk, (B, H, Nk, d), q, accumulate_dkv)
+    dv = _grad_out("dv", dv, (B, H, Nk, d), q, accumulate_dkv)
     st = lib().ringx_attn_bwd_dkdv(q.data_ptr(), k.data_ptr(), v.data_ptr(), dout.data_ptr(),
                                    lse.data_ptr(), delta.data_ptr(), dk.data_ptr(), dv.data_ptr(),
                                    B, H, Nq, Nk, d, R, _scale(scale, d), _dtype_code(q),
@@ -386,14 +387,11 @@ def ringx_attn_bwd_dkdv(q, k, v, dout, lse, delta, R: int, scale=None, dk=None, 
 
 def ringx_attn_bwd_dq(q, k, v, dout, lse, delta, R: int, scale=None, dq=None, stream=None):
     """Query gradient accumulated over every chunk.  Returns fp32 dq."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v, dout, lse, delta)
     B, H, _, Nq, Nk, d = _qkv(q, k, v)
     _check_grad_inputs(q, dout, lse, delta)
-    if dq is None:
-        dq = torch.empty((B, H, Nq, d), dtype=torch.float32, device=q.device)
-    _dev(dq)
-    _expect("dq", dq, (B, H, Nq, d), torch.float32, q.device)
+    dq = _out("dq", dq, (B, H, Nq, d), torch.float32, q)
     st = lib().ringx_attn_bwd_dq(q.data_ptr(), k.data_ptr(), v.data_ptr(), dout.data_ptr(),
                                  lse.data_ptr(), delta.data_ptr(), dq.data_ptr(), B, H, Nq, Nk, d,
                                  R, _scale(scale, d), _dtype_code(q), _stream(stream))
@@ -404,7 +402,7 @@ def ringx_attn_bwd_dq(q, k, v, dout, lse, delta, R: int, scale=None, dq=None, st
 def ringx_attn_fwd_step(q, k, v, out_acc, lse_acc, first: bool, scale=None, stream=None):
     """One ring step: merge q's attention over the chunk k, v into the running fp32
     (out_acc [B,H,Nq,d], lse_acc [B,H,Nq]) in place (Eq. (5)); first=True starts it."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v, out_acc, lse_acc)
     B, H, _, Nq, Nk, d = _qkv(q, k, v)
     _expect("out_acc", out_acc, (B, H, Nq, d), torch.float32, q.device)
@@ -420,7 +418,7 @@ def ringx_attn_bwd_step(q, k, v, dout, lse, delta, dq_acc, dk, dv, accumulate_dq
                         accumulate_dkv: bool = False, scale=None, stream=None):
     """One ring step of the backward for the chunk k, v: its dk, dv (fp32, written or added to)
     and its contribution to dq_acc (added to, or written when accumulate_dq is False)."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v, dout, lse, delta, dq_acc, dk, dv)
     B, H, _, Nq, Nk, d = _qkv(q, k, v)
     _check_grad_inputs(q, dout, lse, delta)
@@ -438,16 +436,11 @@ def ringx_attn_bwd_step(q, k, v, dout, lse, delta, dq_acc, dk, dv, accumulate_dq
 
 def ringx_attn_fwd_gqa(q, k, v, R: int, scale=None, out=None, lse=None, stream=None):
     """Grouped-query attention: q [B,H,Nq,d], k, v [B,Hkv,Nk,d] with Hkv dividing H."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v)
     B, H, Hkv, Nq, Nk, d = _qkv(q, k, v, heads_kv=True)
-    if out is None:
-        out = torch.empty_like(q)
-    if lse is None:
-        lse = torch.empty((B, H, Nq), dtype=torch.float32, device=q.device)
-    _dev(out, lse)
-    _expect("out", out, q.shape, q.dtype, q.device)
-    _expect("lse", lse, (B, H, Nq), torch.float32, q.device)
+    out = _out("out", out, q.shape, q.dtype, q)
+    lse = _out("lse", lse, (B, H, Nq), torch.float32, q)
     st = lib().ringx_attn_fwd_gqa(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                                   lse.data_ptr(), B, H, Hkv, Nq, Nk, d, R, _scale(scale, d),
                                   _dtype_code(q), _stream(stream))
@@ -458,22 +451,17 @@ def ringx_attn_fwd_gqa(q, k, v, R: int, scale=None, out=None, lse=None, stream=N
 def ringx_attn_bwd_gqa(q, k, v, out, dout, lse, R: int, scale=None, dq=None, dk=None, dv=None,
                        accumulate_dkv=False, stream=None):
     """Backward of ringx_attn_fwd_gqa: fp32 dq [B,H,Nq,d], dk, dv [B,Hkv,Nk,d] (group sums)."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v, out, dout, lse)
     B, H, Hkv, Nq, Nk, d = _qkv(q, k, v, heads_kv=True)
     _expect("out", out, q.shape, q.dtype, q.device)
     _expect("dout", dout, q.shape, q.dtype, q.device)
     _expect("lse", lse, (B, H, Nq), torch.float32, q.device)
-    f32 = dict(dtype=torch.float32, device=q.device)
-    dq = torch.empty((B, H, Nq, d), **f32) if dq is None else dq
-    dk = torch.zeros((B, Hkv, Nk, d), **f32) if dk is None else dk
-    dv = torch.zeros((B, Hkv, Nk, d), **f32) if dv is None else dv
-    _dev(dq, dk, dv)
-    _expect("dq", dq, (B, H, Nq, d), torch.float32, q.device)
-    _expect("dk", dk, (B, Hkv, Nk, d), torch.float32, q.device)
-    _expect("dv", dv, (B, Hkv, Nk, d), torch.float32, q.device)
+    dq = _out("dq", dq, (B, H, Nq, d), torch.float32, q)
+    dk = _grad_out("dk", dk, (B, Hkv, Nk, d), q, accumulate_dkv)
+    dv = _grad_out("dv", dv, (B, Hkv, Nk, d), q, accumulate_dkv)
     nbytes = ringx_bwd_workspace_bytes(B, H, Nq, Nk, d, R, _dtype_code(q))
-    ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=q.device)
+    ws = q.new_empty(max(nbytes, 256), dtype=torch.uint8)
     st = lib().ringx_attn_bwd_gqa(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                                   dout.data_ptr(), lse.data_ptr(), dq.data_ptr(), dk.data_ptr(),
                                   dv.data_ptr(), B, H, Hkv, Nq, Nk, d, R, _scale(scale, d),
@@ -492,7 +480,7 @@ def ringx_attn_bwd_dkdv_ds(q, k, v, dout, lse, delta, R: int, ds, kv_begin: int,
     """dK/dV of K/V heads [kv_begin, kv_begin + kv_count) (of B * Hkv), writing their query
     heads' dS into the uint8 device buffer ds (ringx_bwd_ds_bytes(...) bytes).  Returns fp32
     (dk, dv) [B,Hkv,Nk,d]; rows of other heads are not touched."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v, dout, lse, delta, ds)
     B, H, Hkv, Nq, Nk, d = _qkv(q, k, v, heads_kv=True)
     _check_grad_inputs(q, dout, lse, delta)
@@ -519,16 +507,13 @@ def ringx_attn_bwd_dq_ds(ds, k, q_shape, R: int, kv_begin: int, kv_count: int, s
     """dQ of the query heads of K/V heads [kv_begin, kv_begin + kv_count) from ds as written by
     ringx_attn_bwd_dkdv_ds.  q_shape = (B, H, Nq, d).  Returns fp32 dq [B,H,Nq,d] (rows of other
     heads are not touched)."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(ds, k)
     B, H, Nq, d = (int(x) for x in q_shape)
     if k.dim() != 4 or k.shape[0] != B or k.shape[3] != d:
         raise ValueError(f"k: shape {tuple(k.shape)} does not match q_shape {tuple(q_shape)}")
     Hkv, Nk = int(k.shape[1]), int(k.shape[2])
-    if dq is None:
-        dq = torch.empty((B, H, Nq, d), dtype=torch.float32, device=k.device)
-    _dev(dq)
-    _expect("dq", dq, (B, H, Nq, d), torch.float32, k.device)
+    dq = _out("dq", dq, (B, H, Nq, d), torch.float32, k)
     if ds.device != k.device:
         raise ValueError(f"ds: on {ds.device}, expected {k.device}")
     st = lib().ringx_attn_bwd_dq_ds(ds.data_ptr(), _nbytes(ds), k.data_ptr(), dq.data_ptr(), B, H,
@@ -543,27 +528,23 @@ def ringx_attn_bwd_ds(q, k, v, out, dout, lse, R: int, scale=None, dq=None, dk=N
     """The backward through stored dS (bf16, d = 128): fp32 (dq, dk, dv), dk/dv [B,Hkv,Nk,d].
     Without a workspace, one of ringx_bwd_ds_workspace_bytes(..., kv_per_slab) bytes is
     allocated (slabs of kv_per_slab K/V heads, fewer if B * Hkv is smaller)."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(q, k, v, out, dout, lse)
     B, H, Hkv, Nq, Nk, d = _qkv(q, k, v, heads_kv=True)
     _expect("out", out, q.shape, q.dtype, q.device)
     _expect("dout", dout, q.shape, q.dtype, q.device)
     _expect("lse", lse, (B, H, Nq), torch.float32, q.device)
-    f32 = dict(dtype=torch.float32, device=q.device)
-    dq = torch.empty((B, H, Nq, d), **f32) if dq is None else dq
-    dk = torch.zeros((B, Hkv, Nk, d), **f32) if dk is None else dk
-    dv = torch.zeros((B, Hkv, Nk, d), **f32) if dv is None else dv
-    _dev(dq, dk, dv)
-    _expect("dq", dq, (B, H, Nq, d), torch.float32, q.device)
-    _expect("dk", dk, (B, Hkv, Nk, d), torch.float32, q.device)
-    _expect("dv", dv, (B, Hkv, Nk, d), torch.float32, q.device)
+    dq = _out("dq", dq, (B, H, Nq, d), torch.float32, q)
+    dk = _grad_out("dk", dk, (B, Hkv, Nk, d), q, accumulate_dkv)
+    dv = _grad_out("dv", dv, (B, Hkv, Nk, d), q, accumulate_dkv)
     if workspace is None:
         nbytes = ringx_bwd_ds_workspace_bytes(B, H, Hkv, Nq, Nk, d, R,
                                               max(1, min(int(kv_per_slab), B * Hkv)))
-        workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=q.device)
-    _dev(workspace)
-    if workspace.device != q.device:
-        raise ValueError(f"workspace: on {workspace.device}, expected {q.device}")
+        workspace = q.new_empty(max(nbytes, 256), dtype=torch.uint8)
+    else:
+        _dev(workspace)
+        if workspace.device != q.device:
+            raise ValueError(f"workspace: on {workspace.device}, expected {q.device}")
     st = lib().ringx_attn_bwd_ds(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                                  dout.data_ptr(), lse.data_ptr(), dq.data_ptr(), dk.data_ptr(),
                                  dv.data_ptr(), B, H, Hkv, Nq, Nk, d, R, _scale(scale, d),
@@ -577,18 +558,15 @@ def ringx_tt_tokenize(field, k: int, ratio: int, centre, p: int, sigma=None, out
                       tokens=None, stream=None):
     """One fidelity mode of the multi-fidelity tokenizer: field [C, D, H, W] fp32 on the GPU ->
     tokens [L, C p^3] (fp32 by default).  sigma defaults to k / 2."""
-    torch = _torch()
+    torch = _T or _torch()
     _dev(field)
     if field.dtype != torch.float32:
         raise ValueError("field must be fp32")
     C, D, H, W = field.shape
     out_dtype = out_dtype or torch.float32
     L = (D // (ratio * k * p)) * (H // (ratio * k * p)) * (W // (ratio * k * p))
-    if tokens is None:
-        tokens = torch.empty((L, C * p ** 3), dtype=out_dtype, device=field.device)
-    _dev(tokens)
-    _dtype_code(tokens)
-    _expect("tokens", tokens, (L, C * p ** 3), tokens.dtype, field.device)
+    tokens = _out("tokens", tokens, (L, C * p ** 3), out_dtype if tokens is None else tokens.dtype,
+                  field)
     sigma = float(k) / 2.0 if sigma is None else float(sigma)
     cz, cy, cx = (int(c) for c in centre)
     st = lib().ringx_tt_tokenize(field.data_ptr(), tokens.data_ptr(), C, D, H, W, k, ratio, cz,
