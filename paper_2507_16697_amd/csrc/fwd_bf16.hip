@@ -426,7 +426,10 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void fwd_bf16_kernel(
       for (int kt = 0; kt < C::kKTiles; ++kt)
 #pragma unroll
         for (int rr = 0; rr < 16; ++rr) ma = fmaxf(ma, cur[kt][rr]);
-      const float mnew = fmaxf(m2, max_halves(ma) * c2);
+      float mnew = fmaxf(m2, max_halves(ma) * c2);
+      // a stream may meet scores of -inf alone (keys masked by an infinite feature) that one stream
+      // over all keys would weigh at 0: a finite reference keeps its sums 0 instead of NaN
+      if constexpr (KS > 1) mnew = fmaxf(mnew, -3e38f);
       const float alpha = fast_exp2(m2 - mnew);
       m2 = mnew;
       lc *= alpha;

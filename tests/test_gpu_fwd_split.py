@@ -77,3 +77,22 @@ def test_streams_with_distant_references(d):
         rl = torch.logsumexp(s, -1)
         assert rel_rms_err(to_host_f64(out), ro.cpu().numpy()) <= TOL_BF16_REL_RMS
         assert float((lse.double() - rl).abs().max()) <= 1e-3
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,Nq", [(2, 70), (65, 70)])
+def test_streams_of_masked_keys(H, Nq, d):
+    """Keys masked by a feature of -inf (scores of -inf): streams whose keys are all masked add
+    nothing.  The first tile is not masked, so one stream over all keys needs no care."""
+    gen = torch.Generator().manual_seed(6)
+    q, k, v = (torch.randn((1, H, n, d), generator=gen).mul_(0.5) for n in (Nq, 700, 700))
+    q[..., 0], k[..., 0] = 1.0, 0.0
+    k[:, :, 64:] = 0.0
+    k[:, :, 64:, 0] = -float("inf")
+    q, k, v = (x.bfloat16().cuda() for x in (q, k, v))
+    # one chunk: a chunk with no key at all has no local result
+    out, lse = ringx.ringx_attn_fwd(q, k, v, 1, scale=d ** -0.5)
+    s = (q.double() @ k[:, :, :64].double().transpose(-1, -2).contiguous()) * d ** -0.5
+    ro = torch.softmax(s, -1) @ v[:, :, :64].double()
+    assert rel_rms_err(to_host_f64(out), ro.cpu().numpy()) <= TOL_BF16_REL_RMS
+    assert float((lse.double() - torch.logsumexp(s, -1)).abs().max()) <= 1e-4
