@@ -8,8 +8,8 @@
 // HBM-bound: the filter windows do not overlap, so every subdomain cell is read once and every
 // token feature written once.  The unfiltered crop with patch 1 (Table III's filter 1) is a copy
 // with one thread per cell and contiguous per-token stores.  For k a power of two a wave streams
-// 256 consecutive cells of a row, 4 per lane, through the k^2 rows of its windows and accumulates
-// in registers; the k cells of a window are then summed within the lane (k <= 4) or across k/4
+// 256 consecutive cells, 4 per lane, through the k^2 rows of its windows and accumulates in
+// registers; the k cells of a window are then summed within the lane (k <= 4) or across k/4
 // lanes by butterfly shuffles.  Other k take a plain kernel with one thread per filtered cell.
 // The separable weights w_i w_j w_l come in as kernel arguments (computed on the host,
 // normalised to sum 1).
@@ -21,6 +21,8 @@ namespace ringx {
 namespace {
 
 constexpr int kTokThreads = 256;
+constexpr int kTokBatch = 8;             // field rows that a wave of the row kernel has in flight
+constexpr int64_t kTokGridX = 1 << 22;   // workgroups along x of the row kernel
 // four fp32 cells at 4-byte alignment
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -78,55 +80,98 @@ __global__ __launch_bounds__(kTokThreads) void tt_tokenize_kernel(
   }
 }
 
-// Row-streaming variant, K a power of two.  One wave = one (c, a, b) filtered row segment of 256
-// subdomain cells along x (64 lanes x 4 cells); blockIdx.y picks the segment.
-template <int K>
+// Row-streaming variant, K a power of two.  One wave = 256 subdomain cells (64 lanes x 4 cells): a
+// segment of one (c, a, b) filtered row, the segments of a row in neighbouring waves, or with PACK
+// (rows of at most 128 cells) 2^(6 - log2_lanes) whole rows of 2^log2_lanes lanes each.
+// Bound by how many loads are in flight: a wave that loaded and used one field row at a time, with
+// a branch around each load for the lane at the field's periodic edge, read 5.3 TB/s of a 512^3 x 4
+// field at k = 8 (402 us) and far less of small ones, whose few waves then wait row by row.  Eight
+// rows in flight and no branch between them: 342 us (6.3 TB/s; 6.7 with rows on 16-byte boundaries),
+// 256^3 x 3 77 -> 35 us, 128^3 59 -> 11 us; k = 16 420 -> 340, 240 -> 48 and 229 -> 37 us.  Four
+// rows: 359, 37 and 16 us; sixteen (140 registers, three waves per SIMD): 353, 37 and 12 us.
+template <int K, bool PACK>
 __global__ __launch_bounds__(kTokThreads) void tt_tokenize_rows_kernel(
     const float* __restrict__ field, void* __restrict__ tokens, int C, int D, int H, int W, int sx,
-    int gz, int gy, int gx, int z0, int y0, int x0, int p, TokWeights w, int out_bf16) {
+    int gz, int gy, int gx, int z0, int y0, int x0, int p, TokWeights w, int out_bf16, uint32_t segs,
+    int log2_lanes) {
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * (kTokThreads / 64) + (threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t unit =
+      ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (kTokThreads / 64) + wave;
+  const int64_t row = PACK ? (unit << (6 - log2_lanes)) + (lane >> log2_lanes) : unit / segs;
   if (row >= (int64_t)C * gz * gy) return;
   const int b = (int)(row % gy);
   const int a = (int)((row / gy) % gz);
   const int c = (int)(row / ((int64_t)gy * gz));
-  const int pos = blockIdx.y * 256 + 4 * lane;      // first of this lane's 4 subdomain cells
+  // first of this lane's 4 subdomain cells
+  const int pos = PACK ? 4 * (lane & ((1 << log2_lanes) - 1)) : (int)(unit % segs) * 256 + 4 * lane;
   const bool active = pos < sx;                     // sx is a multiple of K and of 4 when K >= 4
 
-  int xs = x0 + pos;
+  // Every lane reads one quad of cells per field row (4-byte alignment is all a multi-dword load
+  // needs).  A lane whose four cells run over the field's end reads the last four cells of the row,
+  // and its other cells, from the row's start, by a second load; lanes past the subdomain's end read
+  // its last quad along with the lane that owns it.
+  int xs = x0 + (active ? pos : sx - 4);
   xs -= xs >= W ? W : 0;
-  // one 16-byte load when the 4 cells do not wrap (4-byte alignment is all a multi-dword global
-  // load needs, so a subdomain that starts off a 16-byte boundary streams the same way)
-  const bool contiguous = active && xs + 4 <= W;
+  const int over = xs + 4 - W;      // cells past the end, when positive
+  const bool wrap = over > 0;
+  xs = wrap ? W - 4 : xs;
   const float* fc = field + (int64_t)c * D * H * W;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int i = 0; i < K; ++i) {
-    int z = z0 + K * a + i;
-    z -= z >= D ? D : 0;
-    z -= z >= D ? D : 0;
-    for (int j = 0; j < K; ++j) {
+  float acc2[4] = {0.f, 0.f, 0.f, 0.f};
+  constexpr int kBatch = K * K < kTokBatch ? K * K : kTokBatch;   // field rows in flight
+  for (int r0 = 0; r0 < K * K; r0 += kBatch) {
+    const float* rowp[kBatch];
+    float wij[kBatch];
+    f32x4 v[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = (r0 + u) / K, j = (r0 + u) % K;
+      int z = z0 + K * a + i;
+      z -= z >= D ? D : 0;
+      z -= z >= D ? D : 0;
       int y = y0 + K * b + j;
       y -= y >= H ? H : 0;
       y -= y >= H ? H : 0;
-      const float wij = w.w[i] * w.w[j];
-      const float* rowp = fc + ((int64_t)z * H + y) * W;
-      if (contiguous) {
-        // the field is streamed once: non-temporal loads, except for the unfiltered crop (k = 1),
-        // whose short row segments are latency-bound
-        const f32x4u* vp = reinterpret_cast<const f32x4u*>(rowp + xs);
-        const f32x4 v = K > 1 ? __builtin_nontemporal_load(vp) : *vp;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(wij, v[e], acc[e]);
-      } else if (active) {
-        cold_path();
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          int x = xs + e;
-          x -= x >= W ? W : 0;
-          acc[e] = __builtin_fmaf(wij, rowp[x], acc[e]);
-        }
-      }
+      wij[u] = w.w[i] * w.w[j];
+      rowp[u] = fc + ((int64_t)z * H + y) * W;
+      // the field is streamed once: non-temporal loads, except for the unfiltered crop (k = 1),
+      // whose short row segments are latency-bound
+      const f32x4u* vp = reinterpret_cast<const f32x4u*>(rowp[u] + xs);
+      v[u] = K > 1 ? __builtin_nontemporal_load(vp) : *vp;
     }
+    __builtin_amdgcn_sched_barrier(0);
+    if (wrap) {
+      cold_path();
+      f32x4 v2[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) v2[u] = *reinterpret_cast<const f32x4u*>(rowp[u]);
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc2[e] = __builtin_fmaf(wij[u], v2[u][e], acc2[e]);
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(wij[u], v[u][e], acc[e]);
+  }
+  if (wrap) {
+    cold_path();
+    // cells 0 .. 3 - over are the row's last ones, the others its first
+    float cell[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float x = acc2[0];
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        x = e + over == f ? acc[f] : x;
+        x = e + over - 4 == f ? acc2[f] : x;
+      }
+      cell[e] = x;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = cell[e];
   }
   // x weights, then the window sums: within the lane for K <= 4, across K/4 lanes otherwise
   float part[4];
@@ -203,17 +248,29 @@ __global__ __launch_bounds__(kTokThreads) void tt_crop_kernel(
   }
 }
 
+template <int K, bool PACK>
+hipError_t launch_rows(const TokArgs& a, int64_t units, int64_t segs, int log2_lanes) {
+  // workgroups along x, then y: a launch dimension holds less than 2^32 threads
+  const int64_t blocks = (units + kTokThreads / 64 - 1) / (kTokThreads / 64);
+  const int64_t nx = blocks < kTokGridX ? blocks : kTokGridX;
+  const dim3 grid((uint32_t)nx, (uint32_t)((blocks + nx - 1) / nx));
+  hipLaunchKernelGGL((tt_tokenize_rows_kernel<K, PACK>), grid, dim3(kTokThreads), 0, a.stream,
+                     a.field, a.tokens, (int)a.C, (int)a.D, (int)a.H, (int)a.W, (int)(a.gx * K),
+                     (int)a.gz, (int)a.gy, (int)a.gx, (int)a.z0, (int)a.y0, (int)a.x0, (int)a.p,
+                     a.w, a.out_bf16 ? 1 : 0, (uint32_t)segs, log2_lanes);
+  return hipGetLastError();
+}
+
 template <int K>
 hipError_t launch_rows(const TokArgs& a) {
-  const int64_t rows = a.C * a.gz * a.gy;
-  const int sx = (int)(a.gx * K);
-  dim3 grid((uint32_t)((rows + kTokThreads / 64 - 1) / (kTokThreads / 64)),
-            (uint32_t)((sx + 255) / 256));
-  hipLaunchKernelGGL((tt_tokenize_rows_kernel<K>), grid, dim3(kTokThreads), 0, a.stream, a.field,
-                     a.tokens, (int)a.C, (int)a.D, (int)a.H, (int)a.W, sx, (int)a.gz, (int)a.gy,
-                     (int)a.gx, (int)a.z0, (int)a.y0, (int)a.x0, (int)a.p, a.w,
-                     a.out_bf16 ? 1 : 0);
-  return hipGetLastError();
+  const int64_t rows = a.C * a.gz * a.gy, sx = a.gx * K;
+  if (sx > 128) {
+    const int64_t segs = (sx + 255) / 256;
+    return launch_rows<K, false>(a, rows * segs, segs, 6);
+  }
+  int l = 0;   // lanes of a row, a power of two that holds whole windows
+  while ((4 << l) < sx) ++l;
+  return launch_rows<K, true>(a, (rows + (64 >> l) - 1) >> (6 - l), 1, l);
 }
 
 }  // namespace
@@ -235,8 +292,8 @@ hipError_t launch_tt_tokenize(const TokArgs& a) {
   }
   // the row kernel needs 4-cell lane groups inside the subdomain row: sx % 4 == 0
   const int64_t sx = a.gx * a.k;
-  const int64_t rows = a.C * a.gz * a.gy;
-  if (sx % 4 == 0 && (sx + 255) / 256 <= 65535 && (rows + 3) / 4 <= 0xffffffffll) {
+  const int64_t units = a.C * a.gz * a.gy * ((sx + 255) / 256);
+  if (sx % 4 == 0 && units / (kTokThreads / 64) < 65535 * kTokGridX) {
     switch (a.k) {
       case 1: return launch_rows<1>(a);
       case 2: return launch_rows<2>(a);

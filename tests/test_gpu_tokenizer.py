@@ -74,3 +74,25 @@ def test_tokenizer_generic_kernel(shape, k, ratio, p, centre):
     torch.cuda.synchronize()
     ref = oracle.tt_tokenize(f.astype(np.float64), k, ratio, centre, p, float(np.float32(1.1)))
     assert max_abs_err(tok.cpu().numpy(), ref) <= TOL_F32
+
+
+@pytest.mark.parametrize("W,ratio,k", [(4, 1, 4), (8, 1, 2), (24, 1, 8), (96, 1, 16), (128, 1, 4),
+                                       (132, 1, 4), (256, 1, 8), (264, 1, 8), (520, 1, 8),
+                                       (288, 1, 32), (128, 2, 1), (384, 2, 2)])
+def test_tokenizer_row_edges(W, ratio, k):
+    """Rows of one lane up to several wave segments (and several rows per wave), with the field's
+    periodic edge before, inside at each of its three places and behind a lane's four cells.  Cells
+    outside the subdomain are NaN and must not reach a token."""
+    C, n = 3, 2 * k
+    sx = W // ratio
+    f = _field(64 + W + k, (C, n * ratio, n * ratio, W))
+    for cx in (0, 1, 2, 3, sx // 2, W - 1):
+        centre = (n * ratio - 1, 1, cx)
+        g = f.copy()
+        if ratio > 1:
+            x = (np.arange(sx) + cx - sx // 2) % W
+            g[..., np.setdiff1d(np.arange(W), x)] = np.nan
+        tok = ringx.ringx_tt_tokenize(torch.from_numpy(g).cuda(), k, ratio, centre, 1)
+        torch.cuda.synchronize()
+        ref = oracle.tt_tokenize(f.astype(np.float64), k, ratio, centre, 1, k / 2.0)
+        assert max_abs_err(tok.cpu().numpy(), ref) <= TOL_F32, cx
