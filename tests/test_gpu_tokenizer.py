@@ -78,7 +78,8 @@ def test_tokenizer_generic_kernel(shape, k, ratio, p, centre):
 
 @pytest.mark.parametrize("W,ratio,k", [(4, 1, 4), (8, 1, 2), (24, 1, 8), (96, 1, 16), (128, 1, 4),
                                        (132, 1, 4), (256, 1, 8), (264, 1, 8), (520, 1, 8),
-                                       (288, 1, 32), (128, 2, 1), (384, 2, 2)])
+                                       (288, 1, 32), (128, 2, 1), (384, 2, 2),
+                                       (520, 1, 4), (1032, 1, 8)])
 def test_tokenizer_row_edges(W, ratio, k):
     """Rows of one lane up to several wave segments (and several rows per wave), with the field's
     periodic edge before, inside at each of its three places and behind a lane's four cells.  Cells
