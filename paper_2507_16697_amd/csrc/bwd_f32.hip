@@ -23,6 +23,7 @@
 #include "ringx_kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ringx {
 namespace {
@@ -97,12 +98,12 @@ __device__ __forceinline__ void dkdv_tile(const BwdF32Args& A, const F32Dims<NS,
   int64_t blk = (total * kp) >> ksl;
   const int64_t end = (total * (kp + 1)) >> ksl;
   int64_t head = qh0 + blk / nqb, i0 = 16 * (blk % nqb);
-  // Queries past the end read as zero rows with zero lse and D: P = 1 meets dO = 0, dS = 0.  Both
-  // forms of a row block are loaded together, so that the second finds its lines in L1 (4% at
+  // Both forms of a row block are loaded together, so that the second finds its lines in L1 (4% at
   // d = 100), except where the four fragments would not fit the 256 registers of a wave.
   constexpr bool kQcEarly = NS < 7;
-  for (; blk < end; ++blk) {
-    const int rows = (int)min<int64_t>(16, A.Nq - i0);
+  // A head's ragged last block is code of its own: its mask in the common loop, as a select or as a
+  // branch, costs 4-8% (8 heads x 4096 x 4096, d = 64: 657 us, 665 with the block apart, 691 and 716).
+  auto block = [&](int rows, auto ragged) {
     const int64_t row0 = head * A.Nq + i0;
     const RowBlock qb(A.q, row0, d, rows), ob(A.dout, row0, d, rows);
     RowFrag<NS> qa, oa;
@@ -124,8 +125,23 @@ __device__ __forceinline__ void dkdv_tile(const BwdF32Args& A, const F32Dims<NS,
       p[r] = expf(__builtin_fmaf(s[r], A.scale, -ls[r]));
       ds[r] = p[r] * (dp[r] - dl[r]);
     }
+    if constexpr (decltype(ragged)::value) {
+      // queries past the end (zero rows) add nothing: a key with an infinite feature makes their
+      // score 0 * inf and their P NaN
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (4 * D.g + r >= rows) p[r] = ds[r] = 0.f;
+    }
     dv.add(oc, p);
     dk.add(qc, ds);
+  };
+  for (; blk < end; ++blk) {
+    if (i0 + 16 <= A.Nq) {
+      block(16, std::false_type{});
+    } else {
+      cold_path();
+      block((int)(A.Nq - i0), std::true_type{});
+    }
     i0 += 16;
     if (i0 >= A.Nq) {
       i0 = 0;

@@ -83,6 +83,42 @@ def test_rows_past_a_chunk_are_not_read_into_it():
     assert torch.isnan(po2[1]).all() and torch.isnan(pl2[1]).all()
 
 
+@pytest.mark.parametrize("d", [24, 64, 128])
+@pytest.mark.parametrize("Nq", [15, 16, 17, 40])
+def test_gradients_of_masked_keys_are_zero(Nq, d):
+    """Keys masked by a feature of -inf weigh nothing in any row (P = exp(-inf) = 0), so their dK and dV
+    are exactly 0 and the other keys' those without them, at query counts that do and do not fill the
+    last block of 16."""
+    H, Nk, live = 2, 70, 50
+    t, x = random_case(63, 1, H, Nq, Nk, d, store="fp32")
+    g = {key: to_device(val, "fp32") for key, val in t.items()}
+    q, k, v, do = g["q"], g["k"], g["v"], g["do"]
+    q[..., 0], k[..., 0], k[:, :, live:, 0] = 1.0, 0.0, -math.inf
+    x["q"][..., 0], x["k"][..., 0] = 1.0, 0.0
+    scale = float(np.float32(d ** -0.5))
+    out, lse = ringx.ringx_attn_fwd(q, k, v, 2, scale=scale)
+    delta = ringx.ringx_bwd_preprocess(out, do, lse)
+    new = dict(dtype=torch.float32, device="cuda")
+    noalloc = [torch.empty((1, H, n, d), **new) for n in (Nq, Nk, Nk)]
+    step = [torch.empty((1, H, n, d), **new) for n in (Nq, Nk, Nk)]
+    got = {"bwd": ringx.ringx_attn_bwd(q, k, v, out, do, lse, 2, scale=scale)[1:],
+           "gqa": ringx.ringx_attn_bwd_gqa(q, k, v, out, do, lse, 2, scale=scale)[1:],
+           "dkdv": ringx.ringx_attn_bwd_dkdv(q, k, v, do, lse, delta, 2, scale=scale),
+           "noalloc": ringx.ringx_attn_bwd_noalloc(q, k, v, out, do, lse, 2, *noalloc,
+                                                   scale=scale)[1:],
+           "step": ringx.ringx_attn_bwd_step(q, k, v, do, lse, delta, *step, accumulate_dq=False,
+                                             scale=scale)[1:]}
+    torch.cuda.synchronize()
+    kl, vl = x["k"][:, :, :live], x["v"][:, :, :live]
+    ro, rl = oracle.attention(x["q"], kl, vl, scale)
+    _, rk, rv = oracle.attention_bwd(x["q"], kl, vl, ro, x["do"], rl, scale)
+    for name, (dk, dv) in got.items():
+        assert bool((dk[:, :, live:] == 0).all()) and bool((dv[:, :, live:] == 0).all()), name
+        for a, ref in ((dk, rk), (dv, rv)):
+            e = max_abs_err(to_host_f64(a)[:, :, :live], ref)
+            assert e <= TOL_F32 * max(1.0, float(np.max(np.abs(ref)))), (name, e)
+
+
 def test_one_value_everywhere():
     """Equal scores: the output is the mean of V and lse = s + ln Nk at any magnitude."""
     for s in (0.0, 3e4, -3e4):
