@@ -103,6 +103,9 @@ __device__ __forceinline__ void dkdv_tile(const BwdF32Args& A, const F32Dims<NS,
   constexpr bool kQcEarly = NS < 7;
   // A head's ragged last block is code of its own: its mask in the common loop, as a select or as a
   // branch, costs 4-8% (8 heads x 4096 x 4096, d = 64: 657 us, 665 with the block apart, 691 and 716).
+  // At d = 97 .. 112 the second copy costs dK/dV alone 11% (3 x 1531 x 3001, d = 100: 213 -> 237 us)
+  // and the branch gains 4% (205), so there the branch it is.
+  constexpr bool kApart = NS != 7;
   auto block = [&](int rows, auto ragged) {
     const int64_t row0 = head * A.Nq + i0;
     const RowBlock qb(A.q, row0, d, rows), ob(A.dout, row0, d, rows);
@@ -125,7 +128,8 @@ __device__ __forceinline__ void dkdv_tile(const BwdF32Args& A, const F32Dims<NS,
       p[r] = expf(__builtin_fmaf(s[r], A.scale, -ls[r]));
       ds[r] = p[r] * (dp[r] - dl[r]);
     }
-    if constexpr (decltype(ragged)::value) {
+    if (decltype(ragged)::value || (!kApart && rows < 16)) {
+      if (!kApart) cold_path();
       // queries past the end (zero rows) add nothing: a key with an infinite feature makes their
       // score 0 * inf and their P NaN
 #pragma unroll
@@ -136,7 +140,9 @@ __device__ __forceinline__ void dkdv_tile(const BwdF32Args& A, const F32Dims<NS,
     dk.add(qc, ds);
   };
   for (; blk < end; ++blk) {
-    if (i0 + 16 <= A.Nq) {
+    if (!kApart) {
+      block((int)min<int64_t>(16, A.Nq - i0), std::false_type{});
+    } else if (i0 + 16 <= A.Nq) {
       block(16, std::false_type{});
     } else {
       cold_path();
