@@ -236,8 +236,10 @@ hipError_t launch_edge(const BwdArgs& a, bool want_kv, bool want_q) {
   A.H = (int)a.H, A.grp = (int)a.G, A.d = (int)a.d, A.scale = a.scale;
   A.acc_kv = a.accumulate_dkv ? 1 : 0, A.acc_q = a.accumulate_dq ? 1 : 0;
   const int64_t bkv = a.BH / a.G, kb = (a.Nk + 15) / 16, qb = (a.Nq + 15) / 16;
-  // the halves share the launch: each needs only its share of the waves
-  const int64_t all = (want_kv ? kb * bkv : 0) + (want_q ? qb * a.BH : 0);
+  // Both halves count whether or not this launch holds both: sharing a launch, each needs only its
+  // share of the waves, and a half launched alone (the stages of the backward) sums in the same
+  // order, so that the stages give the whole backward's bits.
+  const int64_t all = kb * bkv + qb * a.BH;
   const int ks_kv = f32_split(all, a.G * a.Nq), ks_q = f32_split(all, a.Nk);
   A.ksl_kv = __builtin_ctz(ks_kv), A.ksl_q = __builtin_ctz(ks_q);
   A.tiles_kv = (kb * ks_kv + kF32Waves - 1) / kF32Waves;

@@ -119,6 +119,26 @@ def test_gradients_of_masked_keys_are_zero(Nq, d):
             assert e <= TOL_F32 * max(1.0, float(np.max(np.abs(ref)))), (name, e)
 
 
+@pytest.mark.parametrize("H,Nq,Nk,d", [(3, 1531, 3001, 100), (1, 2000, 16, 8),
+                                       (6, 40, 1500, 33), (4, 700, 1100, 64)])
+def test_stages_compose_bitwise(H, Nq, Nk, d):
+    """The whole backward is its stages bit for bit also where the number of 16-row blocks decides how
+    many waves share one, and so the order of the sums: each half alone as in the common launch."""
+    gen = torch.Generator(device="cuda").manual_seed(64)
+    q, k, v, do = (torch.randn((1, H, n, d), generator=gen, device="cuda")
+                   for n in (Nq, Nk, Nk, Nq))
+    out, lse = ringx.ringx_attn_fwd(q, k, v, 1)
+    delta = ringx.ringx_bwd_preprocess(out, do, lse)
+    dq, dk, dv = ringx.ringx_attn_bwd(q, k, v, out, do, lse, 1)
+    k2, v2 = ringx.ringx_attn_bwd_dkdv(q, k, v, do, lse, delta, 1)
+    q2 = ringx.ringx_attn_bwd_dq(q, k, v, do, lse, delta, 1)
+    step = [torch.empty_like(x) for x in (q, k, v)]
+    ringx.ringx_attn_bwd_step(q, k, v, do, lse, delta, *step, accumulate_dq=False)
+    torch.cuda.synchronize()
+    for name, a, stage, one in zip(("dq", "dk", "dv"), (dq, dk, dv), (q2, k2, v2), step):
+        assert torch.equal(a, stage) and torch.equal(a, one), name
+
+
 def test_one_value_everywhere():
     """Equal scores: the output is the mean of V and lse = s + ln Nk at any magnitude."""
     for s in (0.0, 3e4, -3e4):
