@@ -5,12 +5,15 @@
 // d = 128 kernel in bwd_bf16.hip runs one wave per SIMD on a fixed software-pipelined schedule).
 //
 // One workgroup = 8 (or 4) waves = one K/V head and a tile of 128 (64) keys inside one chunk (a key
-// tile never straddles a chunk boundary; the launch rule is at the end of the file).  With the merged log-sum-exp saved by the forward, every chunk's
+// tile never straddles a chunk boundary; the launch rule is at the end of the file).  With the
+// merged log-sum-exp saved by the forward, every chunk's
 // gradients are independent (arXiv 2507.16697 Sec. III-A: K/V chunk gradients computed per
 // chunk), so the workgroup sweeps every query tile of 64 or 128 queries once -- of every query head
 // that shares the K/V head when G > 1 query heads share one (grouped-query attention).  Of 2 B waves,
-// wave w owns keys 32*(w%B) .. +31 of the tile and query half w/B of every query tile, and keeps
-// fp32 dK^T, dV^T accumulators for its keys in registers.  Per query tile:
+// wave w owns keys 32*(w%B) .. +31 of the tile and the even (w/B = 0) or odd 32-query blocks of the
+// head, and keeps fp32 dK^T, dV^T accumulators for its keys in registers.  So a key's sums run in
+// the same order in every shape of the workgroup, and a chunk's gradients are bitwise the same
+// from a launch of that chunk alone and from one of all chunks.  Per query tile:
 //   S    = Q K^T        A = Q rows (LDS),  B = K rows (LDS)             -> lane = key
 //   D-dP = D + dO (-V)^T A = dO rows (LDS), B = -V rows (LDS), accumulators start at D
 //   P    = exp2(S*scale*log2e + nl_i),  -dS = P (D - dP)                (fp32; nl_i = -lse_i*log2e
@@ -33,7 +36,7 @@ namespace {
 
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-// NW waves = KB key blocks of 32 keys x two halves of the query tile; QB 32-query blocks per wave.
+// NW waves = KB key blocks of 32 keys x the two parities of a tile's 32-query blocks, QB per wave.
 template <int D, int NW, int QB>
 struct DkvCfg {
   static constexpr int kThreads = 64 * NW;
@@ -46,7 +49,7 @@ struct DkvCfg {
   static constexpr int kRowBytes = 2 * D;          // Q, dO, K, V rows
   static constexpr int kDSteps = D / 16;
   static constexpr int kCT = D / 32;
-  static constexpr int kQTile = kBQ * kRowBytes;   // bytes of one Q or dO tile (16 KiB)
+  static constexpr int kQTile = kBQ * kRowBytes;   // bytes of one Q or dO tile (16 KiB at kBQ = 128)
   static constexpr int kKTile = kBK * kRowBytes;   // bytes of the K or V tile
   // LDS carve-up (bytes): the Q and dO buffers, read at every product, first, so that their
   // offsets fit the 16-bit immediate of the LDS reads; K, V, nl and D are read from registers
@@ -133,7 +136,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
   const int n = lane & 31;
   const int g = lane >> 5;
   const int kb = wave % C::kKB;     // key block of this wave
-  const int qh = wave / C::kKB;     // query half of this wave
+  const int qh = wave / C::kKB;     // parity of this wave's 32-query blocks
 
   const uint32_t wg = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t per_bh = (int64_t)R * tiles_per_chunk;
@@ -174,7 +177,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
   issue_rowvals<C::kBQ>(nlb, deltab, lbase + C::kOffL, lbase + C::kOffD, nq - 1, wave, lane);
 
   // per-lane LDS byte offsets (tile-relative)
-  // S / dP: A = Q/dO rows (query qh*kQW + 32*b + n), B = K/V rows (key 32*kb + n); chunk 2s+g
+  // S / dP: A = Q/dO rows (query 64*b + 32*qh + n), B = K/V rows (key 32*kb + n); chunk 2s+g
   int aoff[C::kDSteps];
 #pragma unroll
   for (int s = 0; s < C::kDSteps; ++s) aoff[s] = toff<2 * D>(n, 2 * s + g);   // + row block
@@ -190,27 +193,27 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
 #pragma unroll
     for (int ct = 0; ct < C::kCT; ++ct)
       qtoff[h][ct] = eoff<2 * D>(4 * g + 8 * h + trr, 32 * ct + trc);
-  // the same offsets with this wave's key block (K/V rows) and query half (Q/dO rows, nl and D)
+  // the same offsets with this wave's key block (K/V rows) and first query block (Q/dO rows, nl and D)
   // folded in, as opaque registers: each read then adds only immediates (buffer, block, step)
   int kvo[C::kDSteps], qo[C::kDSteps], tqo[2][C::kCT];
 #pragma unroll
   for (int s = 0; s < C::kDSteps; ++s) {
     kvo[s] = C::kOffK + aoff[s] + 32 * kb * C::kRowBytes;
-    qo[s] = aoff[s] + qh * C::kQW * C::kRowBytes;
+    qo[s] = aoff[s] + 32 * qh * C::kRowBytes;
     asm volatile("" : "+v"(kvo[s]), "+v"(qo[s]));
   }
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int ct = 0; ct < C::kCT; ++ct) {
-      tqo[h][ct] = qtoff[h][ct] + qh * C::kQW * C::kRowBytes;
+      tqo[h][ct] = qtoff[h][ct] + 32 * qh * C::kRowBytes;
       asm volatile("" : "+v"(tqo[h][ct]));
     }
-  int so = C::kOffL + 4 * (qh * C::kQW + 4 * g);   // this lane's first query in the nl array
+  int so = C::kOffL + 4 * (32 * qh + 4 * g);   // this lane's first query in the nl array
   asm volatile("" : "+v"(so));
-  static_assert(C::kOffQ % (2 * C::kQTile) == 0 && C::kQTile >= C::kQW * 2 * C::kRowBytes,
+  static_assert(C::kOffQ % (2 * C::kQTile) == 0 && C::kQTile >= 64 * C::kRowBytes,
                 "Q / dO lane offsets below kQTile: xor with kQTile switches buffers");
-  static_assert(C::kOffL % (4 * C::kBQ * 4) == 0 && 4 * (C::kQW + 4) <= C::kBQ * 4,
+  static_assert(C::kOffL % (4 * C::kBQ * 4) == 0 && 32 + 4 < C::kBQ,
                 "nl / D lane offsets below kBQ floats: xor with kBQ * 4 switches buffers");
 
   const bool key_ok = 32 * kb + n < nvalid;
@@ -268,7 +271,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
 #pragma unroll
     for (int b = 0; b < C::kQB; ++b) {
       sacc[b] = f32x16{};
-      const float* db = reinterpret_cast<const float*>(cd) + 32 * b;
+      const float* db = reinterpret_cast<const float*>(cd) + 64 * b;
       const f32x4 d0 = *reinterpret_cast<const f32x4*>(db);
       const f32x4 d1 = *reinterpret_cast<const f32x4*>(db + 8);
       const f32x4 d2 = *reinterpret_cast<const f32x4*>(db + 16);
@@ -283,7 +286,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
       const bf16x8 bv = *reinterpret_cast<const bf16x8*>(vt + kvo[s]);
 #pragma unroll
       for (int b = 0; b < C::kQB; ++b) {
-        const int rowb = 32 * b * C::kRowBytes;
+        const int rowb = 64 * b * C::kRowBytes;
         const bf16x8 aq = *reinterpret_cast<const bf16x8*>(qt + rowb + qo[s]);
         const bf16x8 ao = *reinterpret_cast<const bf16x8*>(ot + rowb + qo[s]);
         sacc[b] = mfma32(aq, bk, sacc[b]);
@@ -291,7 +294,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
       }
     }
     // P and dS (fp32) -> bf16 B operands.  Accumulator r of block b is query
-    // 32b + 8(r/4) + 4g + r%4; the 8 queries of k-step 2b+h are accumulators 8h .. 8h+7.
+    // 64b + 32qh + 8(r/4) + 4g + r%4; the 8 queries of k-step 2b+h are accumulators 8h .. 8h+7.
     // the vector work goes ahead of the other wave's matrix products on the SIMD
     __builtin_amdgcn_s_setprio(1);
     bf16x8 pf[2 * C::kQB], sf[2 * C::kQB];
@@ -300,8 +303,8 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
       float p[16], dsv[16];
 #pragma unroll
       for (int rq = 0; rq < 4; ++rq) {
-        // nl of 4 consecutive queries qh kQW + 32 b + 8 rq + 4 g ..
-        const f32x4 nl4 = *reinterpret_cast<const f32x4*>(cl + 4 * (32 * b + 8 * rq));
+        // nl of 4 consecutive queries 64 b + 32 qh + 8 rq + 4 g ..
+        const f32x4 nl4 = *reinterpret_cast<const f32x4*>(cl + 4 * (64 * b + 8 * rq));
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float pe = fast_exp2(__builtin_fmaf(sacc[b][4 * rq + e], c2, nl4[e]));
@@ -314,7 +317,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
         cold_path();
 #pragma unroll
         for (int rr = 0; rr < 16; ++rr) {
-          const int qi = qh * C::kQW + 32 * b + 8 * (rr >> 2) + 4 * g + (rr & 3);
+          const int qi = 64 * b + 32 * qh + 8 * (rr >> 2) + 4 * g + (rr & 3);
           if (!key_ok || q0 + qi >= nq) {
             p[rr] = 0.f;
             dsv[rr] = 0.f;
@@ -337,7 +340,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
     // dV^T += dO^T P, dK^T += Q^T dS
 #pragma unroll
     for (int ks = 0; ks < 2 * C::kQB; ++ks) {
-      const int rowb = 16 * ks * C::kRowBytes;
+      const int rowb = (64 * (ks >> 1) + 16 * (ks & 1)) * C::kRowBytes;
 #pragma unroll
       for (int c = 0; c < C::kCT; ++c) {
         const bf16x4 o0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(ot + rowb + tqo[0][c]));
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
     so ^= C::kBQ * 4;
   }
 
-  // the two query halves of a key block add their dK^T / dV^T through LDS
+  // the two waves of a key block add their dK^T / dV^T through LDS
   float* xch = reinterpret_cast<float*>(lds + C::kOffQ);
   const int64_t key = k0 + 32 * kb + n;
   float* dkr = dk + (bh * Nk + key) * D;

@@ -110,6 +110,22 @@ def test_ring_backward_matches_full_backward(d):
     assert rel_rms_err(to_host_f64(rq), oq) <= TOL_BF16_REL_RMS
 
 
+@pytest.mark.parametrize("H,Nk,R", [(40, 400, 4), (43, 300, 3), (100, 250, 2), (90, 260, 3)])
+def test_ring_backward_bitwise_across_launch_shapes(H, Nk, R):
+    """The same where a chunk's dK/dV launch and the full one take workgroups of other shapes (by the
+    number of 128-key tiles, here H R against H): a key's sums do not depend on them."""
+    B, Nq, d = 1, 300, 64
+    t, _ = random_case(49, B, H, Nq, Nk, d, store="bf16", std=0.5)
+    g = {k: to_device(v, "bf16") for k, v in t.items()}
+    bounds = _even_bounds(Nk, R)
+    out, lse = ringx.ringx_attn_fwd(g["q"], g["k"], g["v"], R)
+    _, dk, dv = ringx.ringx_attn_bwd(g["q"], g["k"], g["v"], out, g["do"], lse, R)
+    _, rks, rvs = ring.ring_backward(g["q"], _chunks(g["k"], bounds), _chunks(g["v"], bounds),
+                                     out, g["do"], lse)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.cat(rks, dim=2), dk) and torch.equal(torch.cat(rvs, dim=2), dv)
+
+
 def test_bwd_step_accumulate_dkv():
     B, H, Nq, Nk, d = 1, 2, 64, 200, 128
     t, _ = random_case(46, B, H, Nq, Nk, d, store="bf16", std=2 ** -0.5)
