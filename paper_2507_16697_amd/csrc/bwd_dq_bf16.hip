@@ -419,8 +419,7 @@ hipError_t launch(const BwdArgs& a) {
 }  // namespace
 
 hipError_t launch_bwd_dq_bf16(const BwdArgs& a) {
-  const QueryCut c = query_cut((a.Nq + 255) / 256 * a.BH, a.Nk,
-                               a.d == 64 ? HalfRule{768, 4096} : HalfRule{0, 0});
+  const QueryCut c = query_cut((a.Nq + 255) / 256 * a.BH, a.Nk, dq_cut_rule(a.d));
   if (a.d == 128 && c.ks == 1) return launch<128>(a);
   return launch_bwd_dq_bf16_two_waves(a, c);
 }

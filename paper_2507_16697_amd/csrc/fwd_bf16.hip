@@ -653,7 +653,7 @@ FwdPlan plan(const FwdArgs& a, bool partials) {
       if (rounds(rg) < 0.98 * rounds(p.rg) || (n <= 128 && n * rg <= 1024)) p.rg = rg;
     }
   }
-  p.cut = query_cut(n * p.rg, a.Nk / p.rg, a.d == 64 ? HalfRule{512, 16384} : HalfRule{0, 0});
+  p.cut = query_cut(n * p.rg, a.Nk / p.rg, fwd_cut_rule(a.d));
   // partials, which split over chunks already, take two streams at most (four 128-key chunks of 4
   // heads x 512 queries: 8.9 us four ways, 10.2 two ways, 12.3 whole)
   if (partials && p.cut.ks > 2) p.cut.ks = 2;

@@ -22,10 +22,13 @@ struct QueryCut {
                        // keys ks ways
   bool half = false;   // 4-wave workgroups of 128 queries, three per CU (d = 64)
 };
-// Where a kernel's half-size workgroups win although the rounds are full: n >= from, up to `keys`
-// keys.  from = 0: the kernel has none.
-struct HalfRule {
-  int64_t from, keys;
+// What a kernel gains beyond rounds that are half empty or emptier.  A kernel with half-size workgroups
+// takes them in ragged launches, and in full rounds from n = half_from on, up to half_keys keys;
+// one without (half_from = 0) takes two streams in ragged launches, from split_keys[0] keys on up
+// to two rounds and from split_keys[1] on up to three.
+struct CutRule {
+  int64_t half_from, half_keys;
+  int64_t split_keys[2];
 };
 // n = B H ceil(Nq / 256); `keys` that one workgroup visits.  Measured at 8192 keys, two heads (us; one,
 // two and four streams, *half-size):
@@ -36,21 +39,39 @@ struct HalfRule {
 //   dQ d=128       263 157 199  263 181 212  270 311 316  575 485          576 528          963 1043
 // and at n = 64, 4096 keys: 66 40 28, 88 54 45, 81 46 34 and 138 81 64.  So: four streams as long
 // as one round holds the quarter-size workgroups, two while it holds the half-size ones; where the
-// last round is at most half full, half-size workgroups, which end closer together, or two streams
-// for want of them (at 65536 keys, six heads, n = 288: 2003 -> 1498, 3109 -> 2635, 2598 -> 1927 and
-// 4767 -> 3945).  In full rounds splitting loses, because a tile serves fewer queries, unless three
+// last round is at most half full, half-size workgroups, which end closer together.  In full rounds
+// splitting loses, because a tile serves fewer queries, unless three
 // half-size workgroups on a CU gain more by covering each other's barriers, first and last tiles:
 // the d = 64 forward does up to 16384 keys (n = 1024: 1024 keys 97 -> 85, 4096 301 -> 284, 16384
 // 1130 -> 1072; 2% slower at 262144), dQ up to 4096 keys and from three rounds on (1024 keys 118 ->
 // 110, n = 768 at 2048 keys 160 -> 153, n = 3072 at 4096 1138 -> 1108; n = 512 197 against 204).
-inline QueryCut query_cut(int64_t n, int64_t keys, HalfRule h) {
+// At d = 128, without half-size workgroups, two streams in a ragged launch have a fixed cost (a
+// merge, and a wave's own Q for half as many keys) and pay only where the round they save is long.
+// Speed-up over one stream by n and keys (each range: its five n of 257 .. 896):
+//   forward     300         512         1500        4096        8192        16384       32768
+//   257 .. 384  0.86 0.89   0.91 0.94   0.96 1.05   1.03 1.09   1.02 1.11   1.06 1.12   1.17 1.24
+//   513 .. 640  0.79 0.83   0.85 0.89   0.91 0.94   0.95 0.99   0.98 1.00   0.97 1.09   1.04 1.14
+//   769 .. 896  0.74 0.80   0.79 0.82   0.87 0.91   0.91 0.96   0.93 0.97   0.98 1.05   1.01 1.04
+//   dQ
+//   257 .. 384  1.02 1.06   1.07 1.13   1.07 1.17   1.10 1.11   1.10 1.12   1.12 1.15   1.15 1.26
+//   513 .. 640  0.97 0.99   0.99 1.09   1.01 1.03   0.99 1.04   1.01 1.05   1.04 1.13   1.04 1.12
+//   769 .. 896  0.96 0.98   0.96 0.98   0.98 1.03   0.96 1.00   0.95 0.99   1.00 1.12   1.00 1.02
+inline QueryCut query_cut(int64_t n, int64_t keys, const CutRule& r) {
   QueryCut c;
   const bool ragged = n > 256 && n < 1024 && (n - 1) % 256 < 128;
-  if (h.from > 0 && (ragged || (n >= h.from && keys <= h.keys))) c.half = true;
+  if (r.half_from > 0 && (ragged || (n >= r.half_from && keys <= r.half_keys))) c.half = true;
   else if (n <= 64) c.ks = 4;
-  else if (n <= 128 || ragged) c.ks = 2;
+  else if (n <= 128) c.ks = 2;
+  else if (ragged && n <= 768 && keys >= r.split_keys[n <= 512 ? 0 : 1]) c.ks = 2;
   while (c.ks > 1 && keys < 64 * c.ks) c.ks /= 2;
   return c;
+}
+// half-size forms exist at d = 64 only
+inline CutRule fwd_cut_rule(int64_t d) {
+  return d == 64 ? CutRule{512, 16384, {0, 0}} : CutRule{0, 0, {2048, 16384}};
+}
+inline CutRule dq_cut_rule(int64_t d) {
+  return d == 64 ? CutRule{768, 4096, {0, 0}} : CutRule{0, 0, {0, 1024}};
 }
 
 struct FwdArgs {

@@ -1,0 +1,62 @@
+"""The host rules that pick a launch's form (ringx_kernels.h), compiled and asked on the CPU: a form is
+taken only where it was measured to win."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2507_16697_amd import build as B
+
+ROCM_INCLUDE = "/opt/rocm/include"
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(ROCM_INCLUDE),
+                                reason="needs g++ and the HIP headers")
+
+MAIN = r"""
+#include <cstdio>
+#include "ringx_kernels.h"
+int main() {
+  using namespace ringx;
+  long long kind, d, n, keys;
+  while (std::scanf("%lld %lld %lld %lld", &kind, &d, &n, &keys) == 4) {
+    const QueryCut c = query_cut(n, keys, kind == 0 ? fwd_cut_rule(d) : dq_cut_rule(d));
+    std::printf("%d %d\n", c.ks, c.half ? 1 : 0);
+  }
+}
+"""
+FWD, DQ = 0, 1
+
+
+def _build(tmp_path, main):
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text(main)
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", ROCM_INCLUDE, "-I", B.CSRC,
+                    str(src), "-o", str(exe)], check=True, capture_output=True)
+    return lambda rows: [tuple(map(int, l.split())) for l in subprocess.run(
+        [str(exe)], input="\n".join(" ".join(map(str, r)) for r in rows), text=True, check=True,
+        capture_output=True).stdout.splitlines()]
+
+
+def test_query_cuts(tmp_path):
+    ask = _build(tmp_path, MAIN)
+    # (kernel, d, workgroups of 256 queries, keys) -> (key streams, half-size workgroups)
+    cases = {
+        # one round holds the smaller workgroups
+        (FWD, 128, 1, 4096): (4, 0), (FWD, 64, 64, 4096): (4, 0), (FWD, 128, 65, 4096): (2, 0),
+        (DQ, 128, 128, 4096): (2, 0), (FWD, 128, 129, 4096): (1, 0), (DQ, 128, 256, 4096): (1, 0),
+        # a stream owns at least one tile of 64 keys
+        (FWD, 128, 1, 255): (2, 0), (FWD, 128, 1, 127): (1, 0), (DQ, 64, 100, 100): (1, 0),
+        # ragged rounds at d = 128: only from the key counts on where two streams win
+        (FWD, 128, 257, 200): (1, 0), (FWD, 128, 384, 2047): (1, 0), (FWD, 128, 384, 2048): (2, 0),
+        (FWD, 128, 385, 8192): (1, 0), (FWD, 128, 576, 4096): (1, 0), (FWD, 128, 640, 16384): (2, 0),
+        (FWD, 128, 769, 200): (1, 0), (FWD, 128, 896, 65536): (1, 0),
+        (DQ, 128, 257, 200): (2, 0), (DQ, 128, 384, 128): (2, 0), (DQ, 128, 576, 512): (1, 0),
+        (DQ, 128, 576, 1024): (2, 0), (DQ, 128, 832, 8192): (1, 0),
+        # d = 64: half-size workgroups
+        (FWD, 64, 257, 200): (1, 1), (FWD, 64, 385, 200): (1, 0), (FWD, 64, 512, 16384): (1, 1),
+        (FWD, 64, 1024, 16385): (1, 0), (DQ, 64, 576, 8192): (1, 1), (DQ, 64, 767, 200): (1, 0),
+        (DQ, 64, 768, 4096): (1, 1), (DQ, 64, 768, 4097): (1, 0),
+    }
+    got = dict(zip(cases, ask(cases)))
+    assert got == cases, {k: (got[k], cases[k]) for k in cases if got[k] != cases[k]}
