@@ -39,7 +39,6 @@
 #include "ringx_device.h"
 #include "ringx_kernels.h"
 
-#include <algorithm>
 #include <type_traits>
 
 namespace ringx {
@@ -634,35 +633,9 @@ hipError_t launch(const FwdArgs& a, int64_t RG) {
   return hipGetLastError();
 }
 
-struct FwdPlan {
-  QueryCut cut;
-  int64_t rg = 1;   // chunk groups (partials)
-};
-
-FwdPlan plan(const FwdArgs& a, bool partials) {
-  FwdPlan p;
-  const int64_t n = (a.Nq + 255) / 256 * a.BH;
-  // Partials: chunks are independent, so they are spread over workgroups, over as few groups as give
-  // the fewest rounds for their length (480 workgroups, whose two rounds are nearly full, lose 2% to
-  // four groups), and up to four rounds where one is at most half full (Nq = 2048, 8 chunks of 4096,
-  // 16 heads, d = 128: 664 us whole, 479 in one round, 453 in four).
-  if (partials) {
-    auto rounds = [n](int64_t rg) { return (double)((n * rg + 255) / 256) / (double)rg; };
-    for (int64_t rg = 1; rg < a.R && n * rg < 2048;) {
-      rg = std::min<int64_t>(2 * rg, a.R);
-      if (rounds(rg) < 0.98 * rounds(p.rg) || (n <= 128 && n * rg <= 1024)) p.rg = rg;
-    }
-  }
-  p.cut = query_cut(n * p.rg, a.Nk / p.rg, fwd_cut_rule(a.d));
-  // partials, which split over chunks already, take two streams at most (four 128-key chunks of 4
-  // heads x 512 queries: 8.9 us four ways, 10.2 two ways, 12.3 whole)
-  if (partials && p.cut.ks > 2) p.cut.ks = 2;
-  return p;
-}
-
 template <int D, int MODE>
 hipError_t launch_plan(const FwdArgs& a) {
-  const FwdPlan p = plan(a, MODE == (int)FwdMode::kPartials);
+  const FwdPlan p = fwd_plan((a.Nq + 255) / 256 * a.BH, a.Nk, a.R, D, MODE == (int)FwdMode::kPartials);
   if constexpr (D == 64)
     if (p.cut.half) return launch<D, MODE, 1, 4>(a, p.rg);
   if constexpr (MODE != (int)FwdMode::kPartials)

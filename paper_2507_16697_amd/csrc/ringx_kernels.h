@@ -74,6 +74,36 @@ inline CutRule dq_cut_rule(int64_t d) {
   return d == 64 ? CutRule{768, 4096, {0, 0}} : CutRule{0, 0, {0, 1024}};
 }
 
+struct FwdPlan {
+  QueryCut cut;
+  int64_t rg = 1;   // chunk groups (partials)
+};
+
+// n = B H ceil(Nq / 256) as above, R chunks of Nk keys.
+// Partials: chunks are independent, so they are spread over workgroups, over as few groups as give
+// the fewest rounds for their length (480 workgroups, whose two rounds are nearly full, lose 2% to
+// four groups), and up to four rounds where one is at most half full (Nq = 2048, 8 chunks of 4096,
+// 16 heads, d = 128: 664 us whole, 479 in one round, 453 in four).
+inline FwdPlan fwd_plan(int64_t n, int64_t Nk, int64_t R, int64_t d, bool partials) {
+  FwdPlan p;
+  if (partials) {
+    auto rounds = [n](int64_t rg) { return (double)((n * rg + 255) / 256) / (double)rg; };
+    for (int64_t rg = 1; rg < R && n * rg < 2048;) {
+      rg = 2 * rg < R ? 2 * rg : R;
+      if (rounds(rg) < 0.98 * rounds(p.rg) || (n <= 128 && n * rg <= 1024)) p.rg = rg;
+    }
+  }
+  p.cut = query_cut(n * p.rg, Nk / p.rg, fwd_cut_rule(d));
+  if (partials) {
+    // two streams at most, as the launch is split over chunks already (four 128-key chunks of 4
+    // heads x 512 queries: 8.9 us four ways, 10.2 two ways, 12.3 whole), and only where a chunk, not
+    // just its group, has a tile for each: the streams split one chunk after the other
+    if (p.cut.ks > 2) p.cut.ks = 2;
+    if (Nk / R < 64 * p.cut.ks) p.cut.ks = 1;
+  }
+  return p;
+}
+
 struct FwdArgs {
   const void* q = nullptr;
   const void* k = nullptr;

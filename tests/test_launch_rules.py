@@ -25,6 +25,18 @@ int main() {
   }
 }
 """
+PARTIALS_MAIN = r"""
+#include <cstdio>
+#include "ringx_kernels.h"
+int main() {
+  using namespace ringx;
+  long long n, Nk, R, d;
+  while (std::scanf("%lld %lld %lld %lld", &n, &Nk, &R, &d) == 4) {
+    const FwdPlan p = fwd_plan(n, Nk, R, d, true);
+    std::printf("%d %lld\n", p.cut.ks, (long long)p.rg);
+  }
+}
+"""
 FWD, DQ = 0, 1
 
 
@@ -60,3 +72,15 @@ def test_query_cuts(tmp_path):
     }
     got = dict(zip(cases, ask(cases)))
     assert got == cases, {k: (got[k], cases[k]) for k in cases if got[k] != cases[k]}
+
+
+def test_partials_streams_have_tiles(tmp_path):
+    """Streams split the chunks of a group one after the other, so what counts is a chunk's length, also
+    where a workgroup takes several short chunks."""
+    ask = _build(tmp_path, PARTIALS_MAIN)
+    rows = [(5, 26416, 208, 128), (14, 9525, 75, 128), (27, 4826, 38, 128), (2, 8000, 4000, 128)]
+    rows += [(n, c * R, R, d) for d in (64, 128) for n in (1, 5, 20, 130, 300, 576, 900)
+             for R in (1, 2, 3, 8, 100, 700) for c in (1, 40, 64, 127, 128, 5000)]
+    for (n, Nk, R, d), (ks, rg) in zip(rows, ask(rows)):
+        assert 1 <= rg <= R and ks in (1, 2)
+        assert ks == 1 or Nk // R >= 64 * ks, (n, Nk, R, d, ks, rg)
