@@ -445,10 +445,7 @@ hipError_t launch_bwd_dq_ds(const DsArgs& a) {
   using C = DqsCfg;
   const int64_t nqg = (a.Nq + C::kBQ - 1) / C::kBQ;
   const int64_t nwg = a.nh * nqg;
-  // Up to 128 query groups, which leave half of the chip's CUs without work and the others with one
-  // workgroup to hide its own loads: 64 groups x 16384 keys 191 -> 90 us, 128 groups 236 -> 176,
-  // 192 groups even, 256 groups 305 against 341.
-  if (nwg <= 128) {
+  if (dq_ds_streams(a.nh, a.Nq, a.Nk, a.R)) {
     const int64_t nsw = a.nh * ((a.Nq + 31) / 32);
     hipLaunchKernelGGL(bwd_dq_ds_stream_kernel, dim3((uint32_t)nsw), dim3(256), 0, a.stream,
                        static_cast<const char*>(a.ds), static_cast<const __bf16*>(a.k), a.dq,

@@ -104,6 +104,27 @@ inline FwdPlan fwd_plan(int64_t n, int64_t Nk, int64_t R, int64_t d, bool partia
   return p;
 }
 
+// dQ from stored dS: the key-stream kernel (32 queries per workgroup, one of them to a CU) for slabs
+// that leave half of the CUs or more without a group of 128 queries and the others with one group
+// to hide its own loads.  Its speed-up over the 128-query kernel, R = 1, by keys:
+//   groups x queries     32    128   256   512   1000  2000  4000  8000  16000
+//   32 x 128             1.16  1.20  1.31  1.48  1.63  1.80  1.91  1.98  2.04
+//   64 x 128             1.13  1.16  1.27  1.40  1.56  1.66  1.79  1.86  2.11
+//   128 x 32             0.86  0.93  1.08  1.30  1.44  1.48  2.24  2.30  2.18
+//   128 x 64             0.96  1.00  1.12  1.33  1.33  1.47  2.06  2.18  2.05
+//   96 x 128             0.71  0.73  0.76  0.83  0.88  0.94  0.97  0.99  1.29
+//   128 x 128            0.70  0.72  0.77  0.82  0.89  0.98  1.33  1.33  1.32
+// (100 chunks of 20 keys, 128 x 128: 1.27; 192 groups even, 256 groups 0.89.)  So: as long as its
+// workgroups fit one round, for more than 64 groups from 256 keys on; in two rounds only where
+// the 128-query kernel walks many tiles.
+inline bool dq_ds_streams(int64_t nh, int64_t Nq, int64_t Nk, int64_t R) {
+  const int64_t groups = nh * ((Nq + 127) / 128), wgs = nh * ((Nq + 31) / 32);
+  const int64_t tiles = R * (((Nk + R - 1) / R + 63) / 64);
+  if (groups > 128) return false;
+  if (wgs <= 256) return groups <= 64 || Nk >= 256;
+  return tiles >= 96;
+}
+
 struct FwdArgs {
   const void* q = nullptr;
   const void* k = nullptr;

@@ -37,6 +37,15 @@ int main() {
   }
 }
 """
+DS_MAIN = r"""
+#include <cstdio>
+#include "ringx_kernels.h"
+int main() {
+  long long nh, Nq, Nk, R;
+  while (std::scanf("%lld %lld %lld %lld", &nh, &Nq, &Nk, &R) == 4)
+    std::printf("%d\n", ringx::dq_ds_streams(nh, Nq, Nk, R) ? 1 : 0);
+}
+"""
 FWD, DQ = 0, 1
 
 
@@ -84,3 +93,14 @@ def test_partials_streams_have_tiles(tmp_path):
     for (n, Nk, R, d), (ks, rg) in zip(rows, ask(rows)):
         assert 1 <= rg <= R and ks in (1, 2)
         assert ks == 1 or Nk // R >= 64 * ks, (n, Nk, R, d, ks, rg)
+
+
+def test_stored_ds_streams(tmp_path):
+    ask = _build(tmp_path, DS_MAIN)
+    # (query heads, queries, keys, chunks) -> key-stream kernel
+    cases = {(1, 100, 32, 1): 1, (2, 4096, 16384, 4): 1, (64, 128, 64, 1): 1, (65, 32, 255, 1): 0,
+             (128, 32, 256, 1): 1, (128, 64, 400, 1): 1, (128, 100, 100, 1): 0, (3, 4096, 2000, 2): 0,
+             (8, 2048, 512, 1): 0, (1, 16384, 4000, 1): 0, (1, 16384, 16384, 1): 1,
+             (4, 4096, 2000, 100): 1, (129, 20, 8000, 1): 0}
+    got = dict(zip(cases, (r[0] for r in ask(cases))))
+    assert got == cases, {k: got[k] for k in cases if got[k] != cases[k]}
