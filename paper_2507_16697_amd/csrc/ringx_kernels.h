@@ -81,16 +81,24 @@ struct FwdPlan {
 
 // n = B H ceil(Nq / 256) as above, R chunks of Nk keys.
 // Partials: chunks are independent, so they are spread over workgroups, over as few groups as give
-// the fewest rounds for their length (480 workgroups, whose two rounds are nearly full, lose 2% to
-// four groups), and up to four rounds where one is at most half full (Nq = 2048, 8 chunks of 4096,
-// 16 heads, d = 128: 664 us whole, 479 in one round, 453 in four).
+// the shortest launch (480 workgroups, whose two rounds are nearly full, lose 2% to four groups),
+// and up to four rounds where one is at most half full (Nq = 2048, 8 chunks of 4096, 16 heads,
+// d = 128: 664 us whole, 479 in one round, 453 in four).  A launch's length is its rounds times the
+// chunks of the largest group; at d = 128 a chunk costs as much as 320 keys more (its stores) and a
+// workgroup 370 (its queries, the first tiles), fitted to the times of whole and grouped launches
+// of 130 .. 2000 workgroups, 2 .. 8 chunks of 300 .. 4000 keys.  Without these two, 200 workgroups
+// of 8 chunks of 300 keys took eight groups and 1.30 times as long as whole (1000 keys: 1.08).
+// d = 64, whose workgroups are half as large in such launches, gained in every grouped launch.
 inline FwdPlan fwd_plan(int64_t n, int64_t Nk, int64_t R, int64_t d, bool partials) {
   FwdPlan p;
   if (partials) {
-    auto rounds = [n](int64_t rg) { return (double)((n * rg + 255) / 256) / (double)rg; };
+    const double chunk = (double)Nk / (double)R + (d == 128 ? 320 : 0), start = d == 128 ? 370 : 0;
+    auto length = [&](int64_t rg) {
+      return (double)((n * rg + 255) / 256) * ((double)((R + rg - 1) / rg) * chunk + start);
+    };
     for (int64_t rg = 1; rg < R && n * rg < 2048;) {
       rg = 2 * rg < R ? 2 * rg : R;
-      if (rounds(rg) < 0.98 * rounds(p.rg) || (n <= 128 && n * rg <= 1024)) p.rg = rg;
+      if (length(rg) < 0.97 * length(p.rg) || (n <= 128 && n * rg <= 1024)) p.rg = rg;
     }
   }
   p.cut = query_cut(n * p.rg, Nk / p.rg, fwd_cut_rule(d));

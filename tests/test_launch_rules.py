@@ -104,3 +104,16 @@ def test_stored_ds_streams(tmp_path):
              (4, 4096, 2000, 100): 1, (129, 20, 8000, 1): 0}
     got = dict(zip(cases, (r[0] for r in ask(cases))))
     assert got == cases, {k: got[k] for k in cases if got[k] != cases[k]}
+
+
+def test_partials_chunk_groups(tmp_path):
+    """Chunk groups only where the rounds they save outweigh what every workgroup and chunk costs, and
+    counted by the largest group."""
+    ask = _build(tmp_path, PARTIALS_MAIN)
+    # (workgroups of 256 queries, keys, chunks, d) -> chunk groups
+    cases = {(200, 2400, 8, 128): 1, (200, 32000, 8, 128): 8, (640, 12000, 3, 128): 3,
+             (1100, 12000, 3, 128): 1, (450, 3600, 8, 128): 1, (640, 16000, 4, 128): 2,
+             (900, 3600, 4, 128): 1, (128, 32768, 8, 128): 8, (128, 32768, 8, 64): 8,
+             (1100, 12000, 3, 64): 1, (640, 4000, 4, 64): 2, (480, 32768, 8, 128): 1}
+    got = dict(zip(cases, (rg for _, rg in ask(cases))))
+    assert got == cases, {k: got[k] for k in cases if got[k] != cases[k]}
