@@ -133,6 +133,44 @@ inline bool dq_ds_streams(int64_t nh, int64_t Nq, int64_t Nk, int64_t R) {
   return tiles >= 96;
 }
 
+// The row-streaming tokenizer kernel on rows of more than 128 cells: one field row in flight instead of
+// eight (then with a row's 256-cell segments in neighbouring waves at k = 2, a whole sweep of rows
+// apart otherwise).
+struct TokRowsForm {
+  bool one_row = false;
+};
+// Measured (us; a kernel that loads with a branch per row / one row, segments near / one row, far /
+// eight rows, near; 4 channels; crops that start on a 16-byte boundary, off one, and on one with
+// the field's edge inside; 64^2 x 512 and 640 with 2 channels):
+//   k = 2   512^3, patch 2     670 769 720    665 739 690    686 763 727    704 751 735
+//           1024^3, ratio 2    761 808 815    751 774 715    767 812 819    789 812 748
+//   k = 4   512^3              390 468 437    384 391 395    391 433 438    374 382 391
+//           1024^3, ratio 2    380 423 424    486 506 433    384 426 429    495 515 422
+//           1024^2 x 1536, r 2 615 686 707    592 628 655    615 684 709    590 629 653
+//   k = 8   512^3              343 389 383    360 382 363    343 381 384    332 353 350
+//           1024^3             2698 3110 3037 2874 2987 2909 2675 3006 3017 2881 2952 3014
+//           1024^3, ratio 2    329 368 366    333 357 359    330 368 368    354 381 357
+//           64^2 x 640         33 52 33       33 34 34       33 33 33       9 10 9
+//   k = 16  512^3              327 432 364    336 367 352    326 359 363    326 348 351
+//           1024^3, ratio 2    313 348 348    314 338 340    316 352 351    360 386 341
+//   k = 4   1024^3              3002 3703 3453  3103 3234 3127  3048 3573 3469  3152 3394 3185
+//   k = 2   64^2 x 512          5.3 6.5 5.1     5.8 5.7 5.4     -               4.9 5.0 4.9
+// Small fields take eight rows: they come from caches, and few waves need the loads in flight.
+// Large ones take one row at k = 2, whose waves are short; where a crop narrower than its field
+// reads whole segments (k = 4: of rows a multiple of 4 KiB apart); at k = 8 for rows of three
+// segments or more that start on a boundary; and at k = 4 for whole rows of the largest fields.
+inline TokRowsForm tok_rows_form(int64_t k, int64_t rows, int64_t sx, int64_t W, int64_t x0) {
+  TokRowsForm f;
+  const int64_t cells = rows * k * k * sx;
+  if (cells < (int64_t(1) << 27)) return f;
+  const bool crop = sx > 256 && sx % 256 == 0 && sx < W;
+  if (k == 2) f.one_row = true;
+  if (k == 4) f.one_row = (crop && W % 1024 == 0) || (sx == W && x0 == 0 && cells >= int64_t(1) << 31);
+  if (k == 8) f.one_row = crop || (sx > 512 && x0 % 4 == 0 && W % 4 == 0);
+  if (k == 16) f.one_row = crop;
+  return f;
+}
+
 struct FwdArgs {
   const void* q = nullptr;
   const void* k = nullptr;

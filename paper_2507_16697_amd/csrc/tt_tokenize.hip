@@ -83,27 +83,30 @@ __global__ __launch_bounds__(kTokThreads) void tt_tokenize_kernel(
 // Row-streaming variant, K a power of two.  One wave = 256 subdomain cells (64 lanes x 4 cells): a
 // segment of one (c, a, b) filtered row, the segments of a row in neighbouring waves, or with PACK
 // (rows of at most 128 cells) 2^(6 - log2_lanes) whole rows of 2^log2_lanes lanes each.  NB field rows
-// are in flight; with NB = 1 the segments of a row are a whole sweep of rows apart (launch_rows).
+// are in flight; with FAR the segments of a row are a whole sweep of rows apart (tok_rows_form).
 // Bound by how many loads are in flight: a wave that loaded and used one field row at a time, with
 // a branch around each load for the lane at the field's periodic edge, read 5.3 TB/s of a 512^3 x 4
 // field at k = 8 (402 us) and far less of small ones, whose few waves then wait row by row.  Eight
 // rows in flight and no branch between them: 342 us (6.3 TB/s; 6.7 with rows on 16-byte boundaries),
 // 256^3 x 3 77 -> 35 us, 128^3 59 -> 11 us; k = 16 420 -> 340, 240 -> 48 and 229 -> 37 us.  Four
 // rows: 359, 37 and 16 us; sixteen (140 registers, three waves per SIMD): 353, 37 and 12 us.
-template <int K, int NB, bool PACK>
+template <int K, int NB, bool PACK, bool FAR>
 __global__ __launch_bounds__(kTokThreads) void tt_tokenize_rows_kernel(
     const float* __restrict__ field, void* __restrict__ tokens, int C, int D, int H, int W, int sx,
     int gz, int gy, int gx, int z0, int y0, int x0, int p, TokWeights w, int out_bf16, uint32_t segs,
     int log2_lanes) {
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // One row at a time the wave's indices and addresses stay per lane: in scalar registers they are a
+  // serial chain that such a short wave does not hide (512^3 x 4, k = 2, patch 2: 713 against 665
+  // us); with eight rows in flight scalar row addresses are the better ones.
+  const int wave = NB == 1 ? threadIdx.x >> 6 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t unit =
       ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (kTokThreads / 64) + wave;
   const int64_t rows = (int64_t)C * gz * gy;
   int64_t row = unit, seg = 0;
   if constexpr (PACK) {
     row = (unit << (6 - log2_lanes)) + (lane >> log2_lanes);
-  } else if constexpr (NB > 1) {
+  } else if constexpr (!FAR) {
     row = unit / segs;
     seg = unit % segs;
   } else {
@@ -260,13 +263,13 @@ __global__ __launch_bounds__(kTokThreads) void tt_crop_kernel(
   }
 }
 
-template <int K, int NB, bool PACK>
+template <int K, int NB, bool PACK, bool FAR>
 hipError_t launch_rows(const TokArgs& a, int64_t units, int64_t segs, int log2_lanes) {
   // workgroups along x, then y: a launch dimension holds less than 2^32 threads
   const int64_t blocks = (units + kTokThreads / 64 - 1) / (kTokThreads / 64);
   const int64_t nx = blocks < kTokGridX ? blocks : kTokGridX;
   const dim3 grid((uint32_t)nx, (uint32_t)((blocks + nx - 1) / nx));
-  hipLaunchKernelGGL((tt_tokenize_rows_kernel<K, NB, PACK>), grid, dim3(kTokThreads), 0, a.stream,
+  hipLaunchKernelGGL((tt_tokenize_rows_kernel<K, NB, PACK, FAR>), grid, dim3(kTokThreads), 0, a.stream,
                      a.field, a.tokens, (int)a.C, (int)a.D, (int)a.H, (int)a.W, (int)(a.gx * K),
                      (int)a.gz, (int)a.gy, (int)a.gx, (int)a.z0, (int)a.y0, (int)a.x0, (int)a.p,
                      a.w, a.out_bf16 ? 1 : 0, (uint32_t)segs, log2_lanes);
@@ -278,20 +281,17 @@ hipError_t launch_rows(const TokArgs& a) {
   const int64_t rows = a.C * a.gz * a.gy, sx = a.gx * K;
   if (sx > 128) {
     const int64_t segs = (sx + 255) / 256;
-    // Long rows that start on a 16-byte boundary: one row at a time, a row's segments far apart, in
-    // a 1024^3 x 4 field (k = 4 two segments, k = 8 four) 362 (measured with a
-    // branch per load, at the same registers and order) and 2576 us, against 396-429 and 2777
-    // with neighbouring segments and eight rows in flight.  Off the boundary that form is even or
-    // better (433 against 425, 2639 against 2978), as it is at k = 16 (2703 against 3024) and at
-    // k = 8 in two segments (see the kernel).
-    if constexpr (K == 4 || K == 8)
-      if (segs > (K == 4 ? 1 : 2) && a.x0 % 4 == 0 && a.W % 4 == 0)
-        return launch_rows<K, 1, false>(a, rows * segs, segs, 6);
-    return launch_rows<K, kTokBatch, false>(a, rows * segs, segs, 6);
+    const int64_t u = rows * segs;
+    const TokRowsForm f = tok_rows_form(K, rows, sx, a.W, a.x0);
+    if constexpr (K == 2)
+      if (f.one_row) return launch_rows<K, 1, false, false>(a, u, segs, 6);
+    if constexpr (K >= 4 && K <= 16)
+      if (f.one_row) return launch_rows<K, 1, false, true>(a, u, segs, 6);
+    return launch_rows<K, kTokBatch, false, false>(a, u, segs, 6);
   }
   int l = 0;   // lanes of a row, a power of two that holds whole windows
   while ((4 << l) < sx) ++l;
-  return launch_rows<K, kTokBatch, true>(a, (rows + (64 >> l) - 1) >> (6 - l), 1, l);
+  return launch_rows<K, kTokBatch, true, false>(a, (rows + (64 >> l) - 1) >> (6 - l), 1, l);
 }
 
 }  // namespace

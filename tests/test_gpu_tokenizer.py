@@ -97,3 +97,31 @@ def test_tokenizer_row_edges(W, ratio, k):
         torch.cuda.synchronize()
         ref = oracle.tt_tokenize(f.astype(np.float64), k, ratio, centre, 1, k / 2.0)
         assert max_abs_err(tok.cpu().numpy(), ref) <= TOL_F32, cx
+
+
+# one field row in flight: fields of 2^27 cells and more (rules and measurements in ringx_kernels.h)
+@pytest.mark.parametrize("k,ratio,cx", [(2, 2, 259), (4, 2, 256), (4, 2, 1022), (8, 2, 259),
+                                        (16, 2, 1021), (8, 1, 512), (8, 1, 1020), (4, 1, 512)])
+def test_tokenizer_large_fields(k, ratio, cx):
+    """Against the same sums in 64 bits, window by window, plane by plane of the filtered field."""
+    C, n = 2, 1024
+    f = torch.empty((C, n, n, n), device="cuda").uniform_(
+        -1, 1, generator=torch.Generator(device="cuda").manual_seed(k * 10 + ratio))
+    centre = (1000, 3, cx)
+    tok = ringx.ringx_tt_tokenize(f, k, ratio, centre, 1)
+    torch.cuda.synchronize()
+    m = n // ratio
+    g = m // k
+    tok = tok.reshape(g, g, g, C)
+    idx = [(torch.arange(m, device="cuda") + c - m // 2) % n for c in centre]
+    u = torch.arange(k, device="cuda", dtype=torch.float64) - (k - 1) / 2.0
+    w = torch.exp(-u * u / (2.0 * (k / 2.0) ** 2))
+    w = w / w.sum()
+    for a in sorted({0, 1, g // 2, g - 1}):
+        for c in range(C):
+            x = f[c].index_select(0, idx[0][a * k:(a + 1) * k]).index_select(1, idx[1])
+            x = x.index_select(2, idx[2]).double()
+            x = (x.reshape(k, g, k, g, k) * w).sum(-1)
+            x = (x * w[:, None]).sum(2)
+            x = (x * w[:, None, None]).sum(0)
+            assert float((tok[a, :, :, c].double() - x).abs().max()) <= TOL_F32, (a, c)

@@ -46,6 +46,15 @@ int main() {
     std::printf("%d\n", ringx::dq_ds_streams(nh, Nq, Nk, R) ? 1 : 0);
 }
 """
+TOK_MAIN = r"""
+#include <cstdio>
+#include "ringx_kernels.h"
+int main() {
+  long long k, rows, sx, W, x0;
+  while (std::scanf("%lld %lld %lld %lld %lld", &k, &rows, &sx, &W, &x0) == 5)
+    std::printf("%d\n", ringx::tok_rows_form(k, rows, sx, W, x0).one_row ? 1 : 0);
+}
+"""
 FWD, DQ = 0, 1
 
 
@@ -116,4 +125,28 @@ def test_partials_chunk_groups(tmp_path):
              (900, 3600, 4, 128): 1, (128, 32768, 8, 128): 8, (128, 32768, 8, 64): 8,
              (1100, 12000, 3, 64): 1, (640, 4000, 4, 64): 2, (480, 32768, 8, 128): 1}
     got = dict(zip(cases, (rg for _, rg in ask(cases))))
+    assert got == cases, {k: got[k] for k in cases if got[k] != cases[k]}
+
+
+def test_tokenizer_rows_in_flight(tmp_path):
+    ask = _build(tmp_path, TOK_MAIN)
+
+    def rows(C, D, H, k):
+        return C * (D // k) * (H // k)
+
+    # (k, filtered rows, cells of a row, field width, first cell) -> one field row in flight
+    cases = {(8, rows(2, 64, 64, 8), 640, 640, 0): 0, (4, rows(2, 64, 64, 4), 4096, 4096, 0): 0,
+             (8, rows(2, 64, 64, 8), 4096, 4096, 0): 0, (4, rows(4, 512, 512, 4), 512, 512, 0): 0,
+             (4, rows(1, 1024, 1024, 4), 1024, 1024, 0): 0,
+             (4, rows(4, 1024, 1024, 4), 1024, 1024, 4): 0,
+             (4, rows(4, 1024, 1024, 4), 1024, 1024, 0): 1,
+             (4, rows(4, 512, 512, 4), 512, 1024, 259): 1,
+             (4, rows(4, 512, 512, 4), 768, 1536, 0): 0, (8, rows(4, 512, 512, 8), 512, 1024, 3): 1,
+             (8, rows(4, 384, 384, 8), 384, 768, 0): 0, (8, rows(4, 512, 512, 8), 512, 512, 0): 0,
+             (8, rows(4, 1024, 1024, 8), 1024, 1024, 3): 0,
+             (8, rows(4, 1024, 1024, 8), 1024, 1024, 508): 1,
+             (16, rows(4, 512, 512, 16), 512, 1024, 1): 1,
+             (16, rows(4, 1024, 1024, 16), 1024, 1024, 0): 0,
+             (2, rows(2, 64, 64, 2), 512, 512, 0): 0, (2, rows(4, 512, 512, 2), 512, 512, 0): 1}
+    got = dict(zip(cases, (r[0] for r in ask(cases))))
     assert got == cases, {k: got[k] for k in cases if got[k] != cases[k]}
