@@ -119,8 +119,9 @@ __device__ __forceinline__ void issue_rowvals(const float* __restrict__ nlb,
   }
 }
 
+// waves per SIMD: three 4-wave workgroups on a CU, two of 8 waves with 32 queries each
 template <int D, int NW, int QB>
-__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void bwd_dkdv_kernel(
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : QB == 1 ? 4 : 1) void bwd_dkdv_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ nl,
     const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv, int BHkv,

@@ -99,7 +99,8 @@ __device__ __forceinline__ void dkdv_tile(const BwdF32Args& A, const F32Dims<NS,
   const int64_t end = (total * (kp + 1)) >> ksl;
   int64_t head = qh0 + blk / nqb, i0 = 16 * (blk % nqb);
   // Both forms of a row block are loaded together, so that the second finds its lines in L1 (4% at
-  // d = 100), except where the four fragments would not fit the 256 registers of a wave.
+  // d = 100), except at d > 96, where the four fragments would spill far more of the 256 registers
+  // of a wave than the 4 to 8 (d <= 112) and 16 to 48 that spill as it is.
   constexpr bool kQcEarly = NS < 7;
   // A head's ragged last block is code of its own: its mask in the common loop, as a select or as a
   // branch, costs 4-8% (8 heads x 4096 x 4096, d = 64: 657 us, 665 with the block apart, 691 and 716).

@@ -171,3 +171,66 @@ def test_inline_mfma_spacing(src, kernel, products, count, tmp_path):
         near_result, near_write = mfma_hazards(code)
         assert near_result is not None and near_result >= MFMA_RESULT_WAIT, (name, near_result)
         assert near_write is None or near_write >= VALU_TO_MFMA_WAIT, (name, near_write)
+
+
+# The fp32 kernels, under the rules of the other sources
+@pytest.mark.parametrize("src", ["fwd_f32.hip", "bwd_f32.hip"])
+def test_fp32_kernels_have_no_packed_fp32_and_no_flat_accesses(src, tmp_path):
+    text = _asm(src, tmp_path)
+    assert not re.search(r"\bv_pk_(add|mul|fma)_f32\b", text)
+    assert not re.search(r"\bs_(store|buffer_store|atomic|dcache_wb)", text)
+    assert not re.search(r"^\s*flat_(load|store|atomic)", text, re.M)
+
+
+def _resources(text):
+    """{mangled name: (vector registers, scratch bytes, LDS bytes)}"""
+    out = {}
+    for b in re.split(r"\n  - \.agpr_count:", text)[1:]:
+        def field(key):
+            return re.search(r"\.%s:\s+(\S+)" % key, b).group(1)
+        out[field("name")] = (int(field("vgpr_count")), int(field("private_segment_fixed_size")),
+                              int(field("group_segment_fixed_size")))
+    return out
+
+
+# Workgroups that are meant to share a CU: (fragment of the kernel's name, workgroups per CU, waves of
+# one, and whether it keeps out of scratch).  A wave of w per SIMD has 512 / w registers, in steps of 8;
+# a CU has 160 KiB of LDS.
+SHARED = [("bwd_bf16_d64.hip", "bwd_dkdv_kernelILi64ELi8ELi1E", 2, 8, True),
+          ("bwd_bf16_d64.hip", "bwd_dkdv_kernelILi64ELi4ELi1E", 3, 4, True),
+          ("bwd_dq_bf16_d64.hip", "bwd_dq_kernelILi64ELi1ELi4ELi32E", 3, 4, True),
+          ("fwd_bf16.hip", "fwd_bf16_kernelILi64ELi0ELi1ELi4E", 3, 4, False),
+          ("fwd_bf16.hip", "fwd_bf16_kernelILi64ELi1ELi1ELi4E", 3, 4, True),
+          ("fwd_bf16.hip", "fwd_bf16_kernelILi64ELi2ELi1ELi4E", 3, 4, True),
+          ("bwd_dq_ds.hip", "bwd_dq_ds_kernel", 2, 4, True)]
+
+
+@pytest.mark.parametrize("src", sorted({s[0] for s in SHARED}))
+def test_workgroups_share_a_cu(src, tmp_path):
+    text = _asm(src, tmp_path)
+    res = _resources(text)
+    for _, frag, groups, waves, no_scratch in (s for s in SHARED if s[0] == src):
+        names = [n for n in res if frag in n]
+        assert len(names) == 1, (frag, names)
+        vgpr, scratch, lds = res[names[0]]
+        per_simd = groups * waves // 4
+        cap = 512 // per_simd // 8 * 8
+        assert vgpr <= cap and groups * lds <= 160 * 1024, (frag, vgpr, cap, lds)
+        assert scratch == 0 or not no_scratch, (frag, scratch)
+        # as the launch bound asks: one register more would spill rather than halve the occupancy
+        body = text[text.index(names[0] + ":"):]
+        occ = int(re.search(r"; Occupancy: (\d+)", body).group(1))
+        assert occ >= per_simd, (frag, occ)
+
+
+# The kernels of whole workgroups, which serve the large launches, and the two-wave kernels of d = 64
+# keep every value in registers
+@pytest.mark.parametrize("src,frag", [("fwd_bf16.hip", r"fwd_bf16_kernelILi(64|128)ELi\dELi[12]ELi8E"),
+                                      ("bwd_bf16_d64.hip", "bwd_dkdv_kernelILi64E"),
+                                      ("bwd_dq_bf16_d64.hip", "bwd_dq_kernelILi64E"),
+                                      ("bwd_dq_bf16_d64.hip", "bwd_dq_kernelILi128ELi2E"),
+                                      ("bwd_dq_ds.hip", "bwd_dq_ds"), ("fwd_f32.hip", "fwd_f32_kernel"),
+                                      ("bwd_f32.hip", r"bwd_f32_kernelILi[1-6]E")])
+def test_no_spills(src, frag, tmp_path):
+    res = {n: r for n, r in _resources(_asm(src, tmp_path)).items() if re.search(frag, n)}
+    assert res and all(r[1] == 0 for r in res.values()), res
