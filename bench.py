@@ -379,40 +379,50 @@ MIX_COUNTERS = [("pmc_stall1", "SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_W
                 ("pmc_stall2", "SQ_INSTS_VALU SQ_INSTS_MFMA SQ_INSTS_LDS SQ_INSTS_SALU "
                  "SQ_INSTS_VALU_TRANS_F32 SQ_BUSY_CYCLES SQ_VALU_MFMA_BUSY_CYCLES SQ_INSTS_VMEM "
                  "GRBM_GUI_ACTIVE")]
-# matrix kernels of the instruction-mix summary: mangled fragment -> label, waves per SIMD
-MIX_KERNELS = [("fwd_bf16_kernelILi128ELi0E", "fwd_bf16_kernel<128, fused merge>", 2),
-               ("bwd_dkdv_kernelILi128ELb0E", "bwd_dkdv_kernel<128>", 1),
-               ("bwd_dq_kernelILi128E", "bwd_dq_kernel<128>", 1),
-               ("fwd_bf16_kernelILi64ELi0E", "fwd_bf16_kernel<64, fused merge>", 2),
-               ("bwd_dkdv_kernelILi64E", "bwd_dkdv_kernel<64>", 2),
-               ("bwd_dq_kernelILi64E", "bwd_dq_kernel<64>", 2)]
+# matrix kernels of the instruction-mix summary: kernel, template arguments -> label, waves per SIMD
+MIX_KERNELS = [("fwd_bf16_kernel", (128, 0, 1, 8), "fwd_bf16_kernel<128, fused merge>", 2),
+               ("bwd_dkdv_kernel", (128, False), "bwd_dkdv_kernel<128>", 1),
+               ("bwd_dq_kernel", (128,), "bwd_dq_kernel<128>", 1),
+               ("fwd_bf16_kernel", (64, 0, 1, 8), "fwd_bf16_kernel<64, fused merge>", 2),
+               ("fwd_bf16_kernel", (64, 0, 1, 4), "fwd_bf16_kernel<64, fused merge>, half-size", 3),
+               ("bwd_dkdv_kernel", (64, 8, 1), "bwd_dkdv_kernel<64>", 4),
+               ("bwd_dq_kernel", (64, 1, 8, 64), "bwd_dq_kernel<64>", 2),
+               ("bwd_dq_kernel", (64, 1, 4, 32), "bwd_dq_kernel<64>, half-size", 3)]
 
-# mangled-name fragment -> (label in the summaries, traffic key, source files of its hash)
+# kernel, template arguments -> (label in the summaries, traffic key, source files of its hash): the
+# forms that the full launches of the profiled workload take
 PROFILE_KERNELS = [
-    ("fwd_bf16_kernelILi128ELi0E", "fwd_bf16_kernel<128, fused merge>", "fwd_bf16",
+    ("fwd_bf16_kernel", (128, 0, 1, 8), "fwd_bf16_kernel<128, fused merge>", "fwd_bf16",
      ["fwd_bf16.hip", "ringx_device.h"]),
-    ("fwd_bf16_kernelILi128ELi1E", "fwd_bf16_kernel<128, partials>", "fwd_bf16_partials",
+    ("fwd_bf16_kernel", (128, 1, 1, 8), "fwd_bf16_kernel<128, partials>", "fwd_bf16_partials",
      ["fwd_bf16.hip", "ringx_device.h"]),
-    ("bwd_dkdv_kernelILi128ELb0E", "bwd_dkdv_kernel<128>", "bwd_dkdv", ["bwd_bf16.hip", "ringx_device.h"]),
-    ("bwd_dkdv_kernelILi128ELb1E", "bwd_dkdv_kernel<128, dS stores>", "bwd_dkdv_store",
+    ("bwd_dkdv_kernel", (128, False), "bwd_dkdv_kernel<128>", "bwd_dkdv",
      ["bwd_bf16.hip", "ringx_device.h"]),
-    ("bwd_dq_ds_kernel", "bwd_dq_ds_kernel", "bwd_dq_ds", ["bwd_dq_ds.hip", "ringx_device.h"]),
-    ("bwd_dq_kernelILi128E", "bwd_dq_kernel<128>", "bwd_dq", ["bwd_dq_bf16.hip", "ringx_device.h"]),
-    ("bwd_pre_bf16_kernelILi128E", "bwd_pre_bf16_kernel<128>", "bwd_pre", ["bwd_pre.hip", "ringx_device.h"]),
-    ("merge_vec4_kernelILb1ELi1E", "merge_vec4_kernel<bf16 out>", "lse_merge", ["merge.hip", "ringx_device.h"]),
+    ("bwd_dkdv_kernel", (128, True), "bwd_dkdv_kernel<128, dS stores>", "bwd_dkdv_store",
+     ["bwd_bf16.hip", "ringx_device.h"]),
+    ("bwd_dq_ds_kernel", (), "bwd_dq_ds_kernel", "bwd_dq_ds", ["bwd_dq_ds.hip", "ringx_device.h"]),
+    ("bwd_dq_kernel", (128,), "bwd_dq_kernel<128>", "bwd_dq", ["bwd_dq_bf16.hip", "ringx_device.h"]),
+    ("bwd_pre_bf16_kernel", (128,), "bwd_pre_bf16_kernel<128>", "bwd_pre",
+     ["bwd_pre.hip", "ringx_device.h"]),
+    ("merge_vec4_kernel", (True, 1), "merge_vec4_kernel<bf16 out>", "lse_merge",
+     ["merge.hip", "ringx_device.h"]),
 ]
 
 
+def _is_kernel(name, kernel, args):
+    """Whether a traced kernel name, mangled or demangled as rocprofv3 prints it, is this kernel with
+    exactly these template arguments."""
+    if not args:
+        return kernel in name
+    mangled = "".join(f"L{'b' if isinstance(a, bool) else 'i'}{int(a)}E" for a in args)
+    plain = ", ".join(str(a).lower() for a in args)
+    return f"{kernel}I{mangled}E" in name or f"{kernel}<{plain}>" in name
+
+
 def _profile_kernel(name):
-    """rocprofv3 prints some names mangled and some demangled: match either form."""
-    demangled = {"ILi128ELi0E": "<128, 0>", "ILi128ELi1E": "<128, 1>", "ILi128ELb0E": "<128, false>",
-                 "ILi128ELb1E": "<128, true>", "ILi128E": "<128>", "ILb1E": "<true>", "ILb1ELi1E": "<true, 1>"}
-    for frag, label, key, files in PROFILE_KERNELS:
-        if frag in name:
+    for kernel, args, label, key, files in PROFILE_KERNELS:
+        if _is_kernel(name, kernel, args):
             return label, key, files
-        for m, dm in demangled.items():
-            if frag.endswith(m) and frag[: -len(m)] + dm in name.replace("(anonymous namespace)::", ""):
-                return label, key, files
     return None
 
 
@@ -516,7 +526,7 @@ def summarize_profiles(root, workload):
             cmd("pmc_WRITE_SIZE", "pmc", "--pmc WRITE_SIZE") + PROFILE_STEP,
             cmd("pmc_copy_FETCH_SIZE", "pmc", "--pmc FETCH_SIZE") + "python -u bench.py --copy-probe",
             cmd("pmc_copy_WRITE_SIZE", "pmc", "--pmc WRITE_SIZE") + "python -u bench.py --copy-probe"]
-    label_of = {key: lab for _, lab, key, _ in PROFILE_KERNELS}
+    label_of = {key: lab for _, _, lab, key, _ in PROFILE_KERNELS}
     md = [f"# HBM traffic per call: {workload} ({shape})", "",
           "Counters: `FETCH_SIZE` and `WRITE_SIZE` (KiB per dispatch, L2-to-fabric traffic, so reads "
           "served by", "the MALL count as fetched), each in a run of its own:", ""]
@@ -669,8 +679,8 @@ def _summarize_instruction_mix(root, workload, prof, cmd):
     for p in paths:
         for r in _read_csv(p):
             name = r["Kernel_Name"]
-            for frag, label, wps in MIX_KERNELS:
-                if frag in name:
+            for kernel, args, label, wps in MIX_KERNELS:
+                if _is_kernel(name, kernel, args):
                     e = tot.setdefault(label, {"wps": wps, "disp": set()})
                     e["disp"].add((p, int(r["Dispatch_Id"])))
                     e[r["Counter_Name"]] = e.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
@@ -691,7 +701,7 @@ def _summarize_instruction_mix(root, workload, prof, cmd):
            "| kernel | waves per SIMD | dispatches | VALU / product | exp / product | LDS / product "
            "| scalar / product | MFMA busy | waiting | not issued | VALU active | LDS active |",
            "|---|---|---|---|---|---|---|---|---|---|---|---|"]
-    for _, label, _ in MIX_KERNELS:
+    for kernel, args, label, _ in MIX_KERNELS:
         e = tot.get(label)
         if not e or not e.get("SQ_INSTS_MFMA") or not e.get("SQ_WAVE_CYCLES"):
             continue
@@ -699,7 +709,7 @@ def _summarize_instruction_mix(root, workload, prof, cmd):
         # GRBM_GUI_ACTIVE is in both passes: the matrix-core busy fraction uses the second's
         cyc = sum(float(r["Counter_Value"]) for r in _read_csv(paths[1])
                   if r["Counter_Name"] == "GRBM_GUI_ACTIVE"
-                  and any(f in r["Kernel_Name"] for f, lab, _ in MIX_KERNELS if lab == label)) / 8
+                  and _is_kernel(r["Kernel_Name"], kernel, args)) / 8
         busy = e.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0) / (cyc * 1024) if cyc else 0.0
         md.append(f"| {label} | {e['wps']} | {len(e['disp']) // 2} | "
                   f"{(e['SQ_INSTS_VALU'] - m) / m:.2f} | {e['SQ_INSTS_VALU_TRANS_F32'] / m:.2f} | "

@@ -83,6 +83,29 @@ def test_traffic_is_reported_only_for_its_source():
     assert bench.load_traffic("no_such_kernel", "ring8_nk262k_d128", "0" * 16) is None
 
 
+@pytest.mark.parametrize("form,key", [
+    ("fwd_bf16_kernel<128, 0, 1, 8>", "fwd_bf16"), ("fwd_bf16_kernel<128, 0, 2, 8>", None),
+    ("fwd_bf16_kernel<128, 0, 4, 8>", None), ("fwd_bf16_kernel<128, 1, 1, 8>", "fwd_bf16_partials"),
+    ("fwd_bf16_kernel<128, 2, 1, 8>", None), ("fwd_bf16_kernel<64, 0, 1, 8>", None),
+    ("bwd_dq_kernel<128>", "bwd_dq"), ("bwd_dq_kernel<128, 2, 8, 64>", None),
+    ("bwd_dq_kernel<64, 1, 8, 64>", None), ("bwd_dkdv_kernel<128, false>", "bwd_dkdv"),
+    ("bwd_dkdv_kernel<128, true>", "bwd_dkdv_store"), ("bwd_dkdv_kernel<64, 8, 1>", None),
+    ("merge_vec4_kernel<true, 1>", "lse_merge"), ("bwd_pre_bf16_kernel<128>", "bwd_pre")])
+def test_profiles_tell_a_kernel_from_its_other_forms(form, key):
+    """A traced name, mangled or demangled, counts for a kernel of the step only in the form that the
+    step's full launches take, not in the forms of launches that are cut."""
+    bench = _bench()
+    kernel, args = form[:-1].split("<")
+    mangled = "".join("Lb%dE" % (a == "true") if a in ("true", "false") else "Li%sE" % a
+                      for a in args.split(", "))
+    for name in (f"_ZN5ringx12_GLOBAL__N_1{len(kernel)}{kernel}I{mangled}EEvPKDF16bS3_i",
+                 f"void ringx::(anonymous namespace)::{form}(__bf16 const*, int)"):
+        got = bench._profile_kernel(name)
+        assert (got[1] if got else None) == key, name
+    assert bench._profile_kernel("ringx::(anonymous namespace)::bwd_dq_ds_kernel(int)")[1] == "bwd_dq_ds"
+    assert bench._profile_kernel("_ZN5ringx12_GLOBAL__N_123bwd_dq_ds_stream_kernelEPKc") is None
+
+
 def test_source_hash_tracks_the_kernel_text():
     bench = _bench()
     a = bench.kernel_source_hash(["merge.hip", "ringx_device.h"])
