@@ -181,6 +181,38 @@ def test_backward_entry_points(store, d):
     _same("gqa dq", gq.t, ref_gq), _same("gqa dk", gk.t, ref_gk), _same("gqa dv", gv.t, ref_gv)
 
 
+# one 256-query workgroup per head: whole workgroups (129 .. 256), at d = 64 half-size ones (257 and,
+# in full rounds, 770), at d = 128 the one-wave dQ, two streams (257) and, with 2100 keys, two streams in
+# the forward too
+@pytest.mark.parametrize("d,H,Nk", [(64, 130, 300), (128, 130, 300), (64, 257, 300), (128, 257, 300),
+                                    (128, 385, 200), (64, 770, 130), (128, 257, 2100)])
+def test_large_launches_stay_inside_their_buffers(d, H, Nk):
+    """The entry points' outputs between guard bands, and every element written, in the forms that launches
+    of many workgroups take."""
+    B, Nq, R = 1, 41, 3
+    f32 = torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(64)
+    q, k, v, do = (torch.randn((B, H, n, d), generator=gen, device="cuda").mul_(0.5).bfloat16()
+                   for n in (Nq, Nk, Nk, Nq))
+    ref_o, ref_l = ringx.ringx_attn_fwd(q, k, v, R)
+    ref = ringx.ringx_attn_bwd(q, k, v, ref_o, do, ref_l, R)
+    ref_po, ref_pl = ringx.ringx_attn_fwd_partials(q, k, v, R)
+    out, lse = Guarded((B, H, Nq, d), torch.bfloat16), Guarded((B, H, Nq), f32)
+    ringx.ringx_attn_fwd(q, k, v, R, out=out.t, lse=lse.t)
+    po, pl = Guarded((R, B, H, Nq, d), f32), Guarded((R, B, H, Nq), f32)
+    ringx.ringx_attn_fwd_partials(q, k, v, R, part_out=po.t, part_lse=pl.t)
+    ao, al = Guarded((B, H, Nq, d), f32), Guarded((B, H, Nq), f32)
+    ringx.ringx_attn_fwd_step(q, k, v, ao.t, al.t, first=True)
+    grads = [Guarded((B, H, n, d), f32) for n in (Nq, Nk, Nk)]
+    ringx.ringx_attn_bwd(q, k, v, ref_o, do, ref_l, R, dq=grads[0].t, dk=grads[1].t, dv=grads[2].t)
+    for name, guarded, want in (("out", out, ref_o), ("lse", lse, ref_l), ("part_out", po, ref_po),
+                                ("part_lse", pl, ref_pl), ("out_acc", ao, None), ("lse_acc", al, None),
+                                *zip(("dq", "dk", "dv"), grads, ref)):
+        guarded.check(name)
+        if want is not None:
+            _same(name, guarded.t, want)
+
+
 @pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
 def test_tokenizer_entry_point(out_dtype):
     C, k, ratio, p = 3, 4, 2, 2

@@ -152,3 +152,70 @@ def test_shifted_scores_backward(d, shift):
         assert e <= TOL_BF16_REL_RMS, (key, e)
     for key, e in frac.items():
         assert e <= 1.0, (key, e)
+
+
+# (heads, d): workgroups of 256 queries, one per head, so that the launches take whole workgroups, at
+# d = 64 also half-size ones, and at d = 128 dQ its one-wave kernel or, for 257, two key streams
+FULL_LAUNCHES = [(130, 64), (130, 128), (257, 64), (257, 128), (385, 128), (770, 64)]
+
+
+def _tiled(t, H):
+    """One head's case on H heads, whose rows are that head's rolled by the head's number: launches with
+    many workgroups and a reference that is computed once."""
+    return {key: torch.stack([torch.roll(val[0, 0], h if key in ("q", "do") else 0, dims=0)
+                              for h in range(H)])[None].contiguous() for key, val in t.items()}
+
+
+@pytest.mark.parametrize("H,d", FULL_LAUNCHES)
+@pytest.mark.parametrize("total,sign", [(400.0, 1), (5000.0, 1), (5000.0, -1)])
+def test_score_ramp_forward_whole_workgroups(H, d, total, sign):
+    """test_score_ramp_forward in launches of many workgroups: references that move and accumulators that
+    are rescaled after the first tile, in ragged chunks of several tiles."""
+    Nq, Nk, R = 70, 800, 3
+    bits, x, scale = _ramp_case(8, 1, 1, Nq, Nk, d, total, sign)
+    g = _tiled({key: to_device(val, "bf16") for key, val in bits.items()}, H)
+    out, lse = ringx.ringx_attn_fwd(g["q"], g["k"], g["v"], R, scale=scale)
+    po, pl = ringx.ringx_attn_fwd_partials(g["q"], g["k"], g["v"], R, scale=scale)
+    bounds = [ringx.ringx_chunk_bounds(Nk, R, r) for r in range(R)]
+    so, sl = ring.ring_forward(g["q"], [g["k"][:, :, lo:hi].contiguous() for lo, hi in bounds],
+                               [g["v"][:, :, lo:hi].contiguous() for lo, hi in bounds], scale=scale)
+    torch.cuda.synchronize()
+    ref_o, ref_l = (r[0, 0] for r in oracle.attention(x["q"], x["k"], x["v"], scale))
+    ref_po, ref_pl = oracle.attention_partials(x["q"], x["k"], x["v"], scale, R)
+    av = oracle.attention(x["q"], x["k"], np.abs(x["v"]), scale)[0][0, 0]
+    lim = 1.5 * 2.0 ** -8 * (av + np.abs(ref_o)) + 1e-5 * float(np.max(np.abs(ref_o)))
+    for h in sorted({0, 1, H // 2, H - 1}):
+        for name, o, l in (("out", out, lse), ("ring", so, sl)):
+            e = np.abs(np.roll(to_host_f64(o[0, h]), -h, axis=0) - ref_o) / lim
+            assert float(np.max(e)) <= 1.0, (name, h, float(np.max(e)))
+            assert max_abs_err(np.roll(to_host_f64(l[0, h]), -h, axis=0), ref_l) <= TOL_BF16_LSE, name
+        for r in range(R):
+            got = np.roll(to_host_f64(po[r, 0, h]), -h, axis=0)
+            assert rel_rms_err(got, ref_po[r, 0, 0]) <= TOL_BF16_REL_RMS, (r, h)
+            got = np.roll(to_host_f64(pl[r, 0, h]), -h, axis=0)
+            assert max_abs_err(got, ref_pl[r, 0, 0]) <= TOL_BF16_LSE, (r, h)
+
+
+@pytest.mark.parametrize("H,d", FULL_LAUNCHES)
+@pytest.mark.parametrize("shift", [-200.0, 200.0])
+def test_shifted_scores_backward_whole_workgroups(H, d, shift):
+    """test_shifted_scores_backward in launches of many workgroups: lse near -193, where a padded key slot
+    that is not masked would give exp(-lse) = inf, with ragged chunks of several tiles."""
+    Nq, Nk, R = 70, 500, 3
+    bits, x, scale = _shifted_case(12, 1, 1, Nq, Nk, d, shift)
+    g = _tiled({key: to_device(val, "bf16") for key, val in bits.items()}, H)
+    out, lse = ringx.ringx_attn_fwd(g["q"], g["k"], g["v"], R, scale=scale)
+    dq, dk, dv = ringx.ringx_attn_bwd(g["q"], g["k"], g["v"], out, g["do"], lse, R, scale=scale)
+    torch.cuda.synchronize()
+    ref_o, ref_l = oracle.attention(x["q"], x["k"], x["v"], scale)
+    ref = dict(zip(("dq", "dk", "dv"),
+                   oracle.attention_bwd(x["q"], x["k"], x["v"], ref_o, x["do"], ref_l, scale)))
+    bnd = dict(zip(("dq", "dk", "dv"), rounding_bounds(x, x["k"], x["v"], ref_o, ref_l, scale)[1:]))
+    assert all(bool(torch.isfinite(t).all()) for t in (out, lse, dq, dk, dv))
+    for h in sorted({0, 1, H // 2, H - 1}):
+        assert max_abs_err(np.roll(to_host_f64(lse[0, h]), -h, axis=0), ref_l[0, 0]) <= TOL_BF16_LSE
+        for name, t, roll in (("dq", dq, -h), ("dk", dk, 0), ("dv", dv, 0)):
+            r = ref[name][0, 0]
+            lim = 1.5 * bnd[name][0, 0] + 1e-5 * max(1.0, float(np.max(np.abs(r))))
+            e = np.abs(np.roll(to_host_f64(t[0, h]), roll, axis=0) - r) / lim
+            assert float(np.max(e)) <= 1.0, (name, h, float(np.max(e)))
