@@ -191,10 +191,18 @@ def _expect(name, t, shape, dtype, device):
         raise ValueError(f"{name}: on {t.device}, expected {device}")
 
 
+def _new(shape, dtype, like):
+    """A new plain tensor on `like`'s device (new_empty is the faster call, but gives a subclass's
+    own type)."""
+    if type(like) is _T.Tensor:
+        return like.new_empty(shape, dtype=dtype)
+    return _T.empty(shape, dtype=dtype, device=like.device)
+
+
 def _out(name, t, shape, dtype, like):
     """The caller's output buffer, checked, or a new one on `like`'s device."""
     if t is None:
-        return like.new_empty(shape, dtype=dtype)
+        return _new(shape, dtype, like)
     _dev(t)
     _expect(name, t, shape, dtype, like.device)
     return t
@@ -203,7 +211,7 @@ def _out(name, t, shape, dtype, like):
 def _grad_out(name, t, shape, like, accumulate):
     """An fp32 gradient buffer that the call overwrites, or adds to (then a new one starts at 0)."""
     if t is None and accumulate:
-        return like.new_zeros(shape, dtype=_T.float32)
+        return _new(shape, _T.float32, like).zero_()
     return _out(name, t, shape, _T.float32, like)
 
 
@@ -254,7 +262,7 @@ def ringx_attn_fwd(q, k, v, R: int, scale=None, out=None, lse=None, stream=None)
     torch = _T or _torch()
     _dev(q, k, v)
     B, H, _, Nq, Nk, d = _qkv(q, k, v)
-    out = _out("out", out, q.shape, q.dtype, q)
+    out = torch.empty_like(q) if out is None else _out("out", out, q.shape, q.dtype, q)
     lse = _out("lse", lse, (B, H, Nq), torch.float32, q)
     st = lib().ringx_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                               lse.data_ptr(), B, H, Nq, Nk, d, R, _scale(scale, d),
@@ -312,7 +320,7 @@ def ringx_attn_bwd(q, k, v, out, dout, lse, R: int, scale=None, dq=None, dk=None
     code = _dtype_code(q)
     if workspace is None:
         need = ringx_bwd_workspace_bytes(B, H, Nq, Nk, d, R, code)
-        workspace = q.new_empty(max(need, 16), dtype=torch.uint8)
+        workspace = _new(max(need, 16), torch.uint8, q)
     else:
         _dev(workspace)
         if workspace.device != q.device:
@@ -439,7 +447,7 @@ def ringx_attn_fwd_gqa(q, k, v, R: int, scale=None, out=None, lse=None, stream=N
     torch = _T or _torch()
     _dev(q, k, v)
     B, H, Hkv, Nq, Nk, d = _qkv(q, k, v, heads_kv=True)
-    out = _out("out", out, q.shape, q.dtype, q)
+    out = torch.empty_like(q) if out is None else _out("out", out, q.shape, q.dtype, q)
     lse = _out("lse", lse, (B, H, Nq), torch.float32, q)
     st = lib().ringx_attn_fwd_gqa(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                                   lse.data_ptr(), B, H, Hkv, Nq, Nk, d, R, _scale(scale, d),
@@ -461,7 +469,7 @@ def ringx_attn_bwd_gqa(q, k, v, out, dout, lse, R: int, scale=None, dq=None, dk=
     dk = _grad_out("dk", dk, (B, Hkv, Nk, d), q, accumulate_dkv)
     dv = _grad_out("dv", dv, (B, Hkv, Nk, d), q, accumulate_dkv)
     nbytes = ringx_bwd_workspace_bytes(B, H, Nq, Nk, d, R, _dtype_code(q))
-    ws = q.new_empty(max(nbytes, 256), dtype=torch.uint8)
+    ws = _new(max(nbytes, 256), torch.uint8, q)
     st = lib().ringx_attn_bwd_gqa(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                                   dout.data_ptr(), lse.data_ptr(), dq.data_ptr(), dk.data_ptr(),
                                   dv.data_ptr(), B, H, Hkv, Nq, Nk, d, R, _scale(scale, d),
@@ -540,7 +548,7 @@ def ringx_attn_bwd_ds(q, k, v, out, dout, lse, R: int, scale=None, dq=None, dk=N
     if workspace is None:
         nbytes = ringx_bwd_ds_workspace_bytes(B, H, Hkv, Nq, Nk, d, R,
                                               max(1, min(int(kv_per_slab), B * Hkv)))
-        workspace = q.new_empty(max(nbytes, 256), dtype=torch.uint8)
+        workspace = _new(max(nbytes, 256), torch.uint8, q)
     else:
         _dev(workspace)
         if workspace.device != q.device:

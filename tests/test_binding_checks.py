@@ -63,3 +63,20 @@ def test_wrappers_refuse_host_tensors():
     q = _t(1, 1, 8, 64)
     with pytest.raises(ValueError, match="GPU"):
         ringx.ringx_attn_fwd(q, q, q, 1)
+
+
+def test_new_buffers_are_plain_tensors():
+    """Buffers that a call makes itself are plain tensors of the type and device asked for, also beside
+    inputs of a subclass; nothing of the subclass's own runs for them."""
+    class Tagged(torch.Tensor):
+        pass
+
+    ringx._torch()
+    for like in (_t(2, 3), _t(2, 3).as_subclass(Tagged), torch.nn.Parameter(_t(2, 3))):
+        for x in (ringx._out("x", None, (4, 5), torch.float32, like),
+                  ringx._grad_out("x", None, (4, 5), like, False),
+                  ringx._grad_out("x", None, (4, 5), like, True)):
+            assert type(x) is torch.Tensor and x.shape == (4, 5) and x.dtype == torch.float32
+            assert not x.requires_grad
+    assert bool((ringx._grad_out("x", None, (4, 5), _t(1), True) == 0).all())
+    assert ringx._new(7, torch.uint8, _t(1)).shape == (7,)
