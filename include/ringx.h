@@ -79,8 +79,11 @@ typedef enum ringx_dtype RINGX_ENUM_BASE { RINGX_FP32 = 0, RINGX_BF16 = 1 } ring
  *   out [B,H,Nq,d] (dtype)  -- softmax(scale q k^T) v over all Nk keys.
  *   lse [B,H,Nq] (fp32)     -- merged log-sum-exp, lse_max + log(den) of Eq. (5); the backward's
  *                              input.
- *   R -- number of ring-step chunks; each chunk's (loc_out, loc_lse) is formed and merged in
- *   registers, in chunk order.
+ *   R -- number of ring-step chunks; results do not depend on it beyond rounding.  Launches that
+ *   fill the GPU form each chunk's loc_lse and merge it in registers, in chunk order; bf16 launches
+ *   whose workgroups split the keys among their waves, and fp32, merge the waves' parts by Eq. (5)
+ *   instead, whose boundaries need not be the chunks'.  How a launch is split follows its sizes
+ *   alone, so repeated calls are bitwise identical.
  */
 ringx_status ringx_attn_fwd(const void* q, const void* k, const void* v, void* out, float* lse,
                             int64_t B, int64_t H, int64_t Nq, int64_t Nk, int64_t d, int64_t R,
@@ -124,8 +127,9 @@ ringx_status ringx_lse_merge(const float* part_out, const float* part_lse, void*
  *   workspace/workspace_bytes -- device scratch of at least ringx_bwd_workspace_bytes(...) bytes,
  *   16-byte aligned, owned by the caller; it receives the per-row statistics of
  *   ringx_bwd_preprocess (D and nl); contents on entry are ignored.
- *   R -- chunk count: no key tile straddles a chunk boundary; results do not depend on R beyond
- *   rounding.  dq, dk and dv are bitwise reproducible.
+ *   R -- chunk count: in bf16 no key tile straddles a chunk boundary, in fp32 it is not looked at;
+ *   results do not depend on R beyond rounding.  dq, dk and dv are bitwise reproducible, and bitwise
+ *   those of the three stages.
  */
 ringx_status ringx_attn_bwd(const void* q, const void* k, const void* v, const void* out,
                             const void* dout, const float* lse, float* dq, float* dk, float* dv,

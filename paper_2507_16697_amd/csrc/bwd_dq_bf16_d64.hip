@@ -1,14 +1,15 @@
-// Recompute backward of ring-chunked attention, dQ part at head size 64: bf16 MFMA with fp32
-// accumulation (gfx950).  At d = 64 a score element carries more vector work per matrix product
-// than one wave can hide behind its own products, so this kernel runs two waves per SIMD (the
-// d = 128 kernel in bwd_dq_bf16.hip runs one wave per SIMD on a fixed software-pipelined schedule).
+// Recompute backward of ring-chunked attention, dQ part at head size 64, and at 128 in launches
+// that are cut: bf16 MFMA with fp32 accumulation (gfx950).  At d = 64 a score element carries more
+// vector work per matrix product than one wave can hide behind its own products, so this kernel runs
+// two waves per SIMD (the d = 128 kernel in bwd_dq_bf16.hip runs one wave per SIMD on a fixed
+// software-pipelined schedule).
 // Where the launch has to be cut smaller (query_cut in ringx_kernels.h) this kernel also serves
 // d = 128, whose one-wave schedule has no room for a second key stream in LDS.
 //
 // Query-stationary, like the forward: one workgroup = 8 waves = one (b, h) and 256 queries (32
 // per wave).  The key/value sequence is streamed chunk by chunk (ring steps, arXiv 2507.16697
-// Sec. III-A) in tiles of 64 keys that never straddle a chunk, double buffered in LDS and filled
-// by direct global->LDS loads one tile ahead.  dQ accumulates over every tile of every chunk in
+// Sec. III-A) in tiles of 64 (or 32) keys that never straddle a chunk, double buffered in LDS and
+// filled by direct global->LDS loads one tile ahead.  dQ accumulates over every tile of every chunk in
 // fp32 registers and is written once, so it needs no atomics (the paper's "gradient for Q
 // accumulated over N steps").  Per tile, with lane = query n and g = lane / 32:
 //   S^T  = K Q^T      A = K rows (LDS),  B = Q^T from registers

@@ -2,7 +2,7 @@
 // cores (tiles and operand layouts in f32_tiles.h).
 //
 // Both halves recompute P_ij = exp(scale q_i.k_j - lse_i) from the merged log-sum-exp and
-// dS_ij = P_ij (dout_i.v_j - D_i); one wave owns 16 stationary rows as B operands and streams 16
+// dS_ij = P_ij (dout_i.v_j - D_i), over all keys whatever their chunk; one wave owns 16 stationary rows as B operands and streams 16
 // rows of the other side at a time:
 //   dK/dV: 16 keys; S = Q K^T, dP = dO V^T (lane: its key, queries 4 g + r), dV^T += dO^T P,
 //          dK^T += Q^T dS, over every query of every query head that shares the K/V head;

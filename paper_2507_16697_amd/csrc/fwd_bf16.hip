@@ -2,11 +2,13 @@
 //
 // One workgroup = 8 waves (two per SIMD) = one (b, h) and a tile of 256 queries (32 per wave), so
 // that each K/V tile brought into LDS serves 256 queries; problems too small or uneven for that
-// take smaller workgroups or split the keys among a workgroup's waves (query_cut in ringx_kernels.h).  The key/value
-// sequence is visited as R chunks (ring steps, arXiv 2507.16697 Sec. III-A), streamed through LDS
-// in tiles of 64 keys that never straddle a chunk boundary.  K and V tiles are double buffered
-// (the on-chip analogue of the paper's ping-pong buffers) and filled by direct global->LDS loads:
-// while tile j is processed, the K tile j+2 and the V tile j+1 are in flight.
+// take smaller workgroups or split the keys among a workgroup's waves (query_cut in
+// ringx_kernels.h).  The key/value sequence is visited as R chunks (ring steps, arXiv 2507.16697
+// Sec. III-A), streamed through LDS in tiles of 64 keys that never straddle a chunk boundary; in
+// fused mode key streams take the whole sequence in tiles of 64 keys (32 for four streams at
+// d = 128) without regard to chunks, whose merge their own then is.  K and V tiles are double
+// buffered (the on-chip analogue of the paper's ping-pong buffers) and filled by direct
+// global->LDS loads: while tile j is processed, the K tile j+2 and the V tile j+1 are in flight.
 //
 // Each wave is software pipelined over key tiles: the MFMAs of S_{j+1} = K_{j+1} Q^T are
 // interleaved with the exponentials and row sums of tile j, so that the matrix cores and the
@@ -27,8 +29,8 @@
 // redone with m moved to its row maximum and the accumulators rescaled.  A lane's sum bounds each
 // of its terms, so every probability stays below 2^32: bf16 and fp32 keep the same relative
 // precision at any magnitude, and a row sum or output accumulator of at most 2^32 per key stays
-// far inside the fp32 range for any realistic V.  At the end of chunk r the
-// wave forms the chunk's log-sum-exp loc_lse_r from the chunk's own row sum and folds it into the
+// far inside the fp32 range for any realistic V.  At the end of chunk r (a workgroup without key
+// streams) the wave forms the chunk's log-sum-exp loc_lse_r from the chunk's own row sum and folds it into the
 // merged lse by Eq. (5).  The output numerator is kept unnormalised: Eq. (5)'s term
 // exp(loc_lse_r - M) loc_out_r equals exp(m - M) times the chunk's unnormalised accumulator, so
 // one accumulator holds the running sum of all chunk terms and the final division by the Eq. (5)
@@ -60,7 +62,7 @@ struct FwdCfg {
   static constexpr int kBK = KS * D > 256 ? 32 : 64;   // keys per tile (LDS holds 4 KS tiles)
   static constexpr int kRowBytes = D * 2;
   static constexpr int kChunks = D / 8;           // 16-byte chunks per row
-  static constexpr int kTileBytes = kBK * kRowBytes;   // 16 KiB (d=128), 8 KiB (d=64)
+  static constexpr int kTileBytes = kBK * kRowBytes;   // 16 KiB (64 keys, d = 128) or 8 KiB
   static constexpr int kKTiles = kBK / 32;        // 32-key blocks per tile
   static constexpr int kDSteps = D / 16;          // MFMA k-steps over the head dim
   static constexpr int kKSteps = kBK / 16;        // MFMA k-steps over the keys
