@@ -40,14 +40,14 @@ struct CutRule {
 // and at n = 64, 4096 keys: 66 40 28, 88 54 45, 81 46 34 and 138 81 64.  So: four streams as long
 // as one round holds the quarter-size workgroups, two while it holds the half-size ones; where the
 // last round is at most half full, half-size workgroups, which end closer together.  In full rounds
-// splitting loses, because a tile serves fewer queries, unless three
-// half-size workgroups on a CU gain more by covering each other's barriers, first and last tiles:
+// splitting loses, because a tile serves fewer queries, unless three half-size workgroups on a CU
+// gain more by covering each other's barriers, first and last tiles:
 // the d = 64 forward does up to 16384 keys (n = 1024: 1024 keys 97 -> 85, 4096 301 -> 284, 16384
 // 1130 -> 1072; 2% slower at 262144), dQ up to 4096 keys and from three rounds on (1024 keys 118 ->
 // 110, n = 768 at 2048 keys 160 -> 153, n = 3072 at 4096 1138 -> 1108; n = 512 197 against 204).
 // At d = 128, without half-size workgroups, two streams in a ragged launch have a fixed cost (a
 // merge, and a wave's own Q for half as many keys) and pay only where the round they save is long.
-// Speed-up over one stream by n and keys (each range: its five n of 257 .. 896):
+// Speed-up over one stream by n and keys (lowest and highest of five n in each range):
 //   forward     300         512         1500        4096        8192        16384       32768
 //   257 .. 384  0.86 0.89   0.91 0.94   0.96 1.05   1.03 1.09   1.02 1.11   1.06 1.12   1.17 1.24
 //   513 .. 640  0.79 0.83   0.85 0.89   0.91 0.94   0.95 0.99   0.98 1.00   0.97 1.09   1.04 1.14

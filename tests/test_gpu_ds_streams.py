@@ -1,6 +1,7 @@
-"""dQ from stored dS through both of its kernels (needs an MI355X): the key-stream kernel (up to 128
-groups of 128 queries per slab) at the edges of its 32-key blocks, 32-query blocks and four streams,
-and the 128-query kernel above it.  Held to the recompute backward: the two paths round the same
+"""dQ from stored dS through both of its kernels (needs an MI355X): the key-stream kernel (slabs of up
+to 64 groups of 128 queries, and of up to 128 where it has enough keys) at the edges of its 32-key
+blocks, 32-query blocks and four streams, in one round of workgroups and in two, and the 128-query
+kernel for the others.  Held to the recompute backward: the two paths round the same
 dS to bf16, so dQ differs by summation order and single roundings only (relative RMS 1e-4)."""
 
 import math
@@ -15,7 +16,8 @@ pytestmark = pytest.mark.gpu
 # (H, Hkv, Nq, Nk, R); groups of 128 queries = H ceil(Nq / 128)
 CASES = [(1, 1, 1, 2, 1), (1, 1, 31, 31, 1), (1, 1, 33, 33, 3), (2, 1, 32, 96, 1),
          (2, 2, 127, 127, 2), (1, 1, 129, 128, 1), (3, 3, 160, 129, 4), (2, 1, 97, 640, 7),
-         (128, 128, 20, 70, 2), (129, 129, 20, 70, 2), (129, 43, 33, 150, 1)]
+         (128, 128, 20, 70, 2), (129, 129, 20, 70, 2), (129, 43, 33, 150, 1),
+         (65, 65, 20, 255, 1), (65, 65, 20, 256, 1), (128, 64, 33, 300, 3), (70, 35, 101, 6200, 2)]
 
 
 @pytest.mark.parametrize("H,Hkv,Nq,Nk,R", CASES)
